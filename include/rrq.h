@@ -339,7 +339,11 @@ int rrq_reconstruct_format(const uint32_t *codes, const void *scales, const floa
  *              4096 inputs, by stage and token count), more tokens 16
  *              per pass; from 128 tokens (groups of 128) tiles of 64 or
  *              128 tokens run as a matrix-core product with the 16-token
- *              tiles' accumulation order (the same results).
+ *              tiles' accumulation order (the same results). Where it is
+ *              faster (groups of 32 and 64; groups of 128 with 3 or 4
+ *              stages, by row and token count) more than 16 tokens take the
+ *              split form below, whose results are closer to the exact value
+ *              and do not depend on n_tokens within the form.
  *   Y          device, float [n_tokens][rows], 4-byte aligned (written).
  *   stream     HIP stream the work is enqueued on.
  *
@@ -351,6 +355,15 @@ int rrq_reconstruct_format(const uint32_t *codes, const void *scales, const floa
  * (11 + |z_t,g|) sum_{i in g} |X[m][i]|, p = groups per row and
  * n = k_stages * (min(p, 4 ceil(p / 16)) + 1),
  * |Y[m][o] - exact| <= 1.05 u A (group_size + 2 n + 24).
+ * The split form forms the prefix weight sum_t s_t (Q_t - z_t) in binary32,
+ * splits it into two binary16 operands (to 2^-22 of itself) and takes X to
+ * binary16, both scaled by powers of two that follow their ranges along a
+ * row, so that a value keeps at least 2^-27 of the largest of its 128 inputs;
+ * its error on packages of this library lies about three times below the
+ * products' own (2-norm 4e-7 against 1.3e-6 of the result at 4 stages), and
+ * the bound above holds where the scales of the groups that share 128 inputs
+ * of a row (groups of 32 and 64), and scales and activations along a row,
+ * stay within 2^36 of each other.
  *
  * Returns RRQ_OK, or RRQ_ERR_NULL / _ALIGN / _SHAPE / _GROUP / _STAGES with
  * nothing enqueued, or RRQ_ERR_HIP if the kernel launch failed.

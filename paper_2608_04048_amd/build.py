@@ -14,6 +14,7 @@ import os
 import shutil
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -41,7 +42,8 @@ HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra"]
 SOURCE_FLAGS = {"rrq_linear": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
                 "rrq_decode": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
                 "rrq_batch": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-                "rrq_prefill": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+                "rrq_prefill": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+                "rrq_split": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def hipcc() -> str:
@@ -67,15 +69,18 @@ def build(keep_asm: bool = False) -> str:
     """Compile every source and link librrq.so; returns the library path."""
     cc = hipcc()
     os.makedirs(BUILD_DIR, exist_ok=True)
-    kern_objs = []
-    for name in ("rrq_kernels", "rrq_linear", "rrq_decode", "rrq_batch", "rrq_prefill"):
+    kern_objs, cmds = [], []
+    for name in ("rrq_kernels", "rrq_linear", "rrq_decode", "rrq_batch", "rrq_prefill",
+                 "rrq_split"):
         obj = os.path.join(BUILD_DIR, name + ".o")
         cmd = [cc, *DEVICE_FLAGS, *SOURCE_FLAGS.get(name, []), f"-I{INCLUDE}", f"-I{CSRC}", "-c",
                os.path.join(CSRC, name + ".hip"), "-o", obj]
         if keep_asm:
             cmd += ["-save-temps=obj"]
-        _run(cmd)
+        cmds.append(cmd)
         kern_objs.append(obj)
+    with ThreadPoolExecutor(max_workers=len(cmds)) as pool:
+        list(pool.map(_run, cmds))
     api_obj = os.path.join(BUILD_DIR, "rrq_api.o")
     _run([cc, "-x", "c++", *HOST_FLAGS, "-D__HIP_PLATFORM_AMD__", f"-I{INCLUDE}", f"-I{CSRC}",
           f"-I{ROCM}/include",

@@ -84,6 +84,15 @@ hipError_t launch_linear_prefill(const uint32_t *codes, const void *scales, cons
                                  int64_t rows, int64_t cols, int k, int zero_point,
                                  int scale_type, const uint16_t *X, int64_t n_tokens, float *Y,
                                  int cus, hipStream_t stream);
+// The split form (more than 16 tokens, any group size; the stage, row and
+// token counts where it is the faster one: linear_split_fits): the prefix
+// weight formed in binary32 and split into two binary16 operands, two
+// matrix-core passes whatever the stage count.
+bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus);
+hipError_t launch_linear_split(const uint32_t *codes, const void *scales, const float *zeros,
+                               int64_t rows, int64_t cols, int G, int k, int zero_point,
+                               int scale_type, const uint16_t *X, int64_t n_tokens, float *Y,
+                               int cus, hipStream_t stream);
 bool linear_decode_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens);
 hipError_t launch_linear_decode(const uint32_t *codes, const void *scales, const float *zeros,
                                 int64_t rows, int64_t cols, int k, int zero_point, int scale_type,

@@ -1,0 +1,705 @@
+// Split form of the stage-sum linear layer (Eq. 20) for more than 16 tokens:
+// Y[m][o] = sum_i X[m][i] W~[o][i] with the prefix weight
+// W~ = sum over stages t < K of s_t (Q_t - z_t) formed once per tile in
+// binary32 and split into two binary16 operands, so that a product takes two
+// matrix-core passes whatever the stage count.
+//
+// Operands (v_mfma_f32_16x16x32_f16, lane l: row / column n = l % 16,
+// k-slice j = l / 16, a chunk = 128 inputs, lane j owning inputs
+// 32 j .. 32 j + 31 of it, block b = inputs 32 j + 8 b .. + 7):
+//   * B: w' = W~ 2^(14 - Ew) in binary32 (Ew a running exponent bound of the
+//     row, see below), hi = f16(w'), lo = f16(w' - hi): hi + lo carries w' to
+//     2^-22 of itself. A code needs no conversion: masked in place it is the
+//     binary16 subnormal Q 2^(p - 24), exact in v_fma_mix_f32, and s_t takes
+//     the factor 2^(24 - p);
+//   * A: x' = x 2^(14 - Ex) in binary16: exact down to 2^-17 (bfloat16 has 8
+//     significant bits, binary16 11), to 2^-25 below.
+// Ex and Ew are running bounds per token and per row: the exponent of the
+// largest value of the quarter's first chunk plus 4 bits of headroom, moved
+// when a later chunk passes it or falls far below it; the accumulators, the
+// MFMAs' own, are then multiplied by the power of two (exact). On weights and
+// activations with outliers that happens in a few of the first chunks.
+//
+// Accumulation order: the chunks of a row in 4 contiguous quarters
+// (ceil(chunks / 4) each), each accumulated from 0 in chunk order (block by
+// block, lo before hi), and the quarters added in order. The order does not
+// depend on the tile shape or on which waves take the quarters, so every
+// token count gives the same results.
+//
+// What bounds it: vector issue. Per chunk of 16 rows a wave forms its B
+// operands with about 330 vector instructions at 4 stages (8 per element)
+// whatever the tokens, and its share of the activations' conversion with
+// about 100 per 16 tokens; a SIMD spends 4 to 5 cycles on each and 10 issue
+// cycles per MFMA, of 16 the MFMA takes. So the tile has as many tokens as
+// registers and LDS allow (256: 16 accumulators and 16 running sums) before
+// it has more rows, and calls with few tiles rather split the quarters over
+// waves than the tokens. Against the forms that multiply every stage's codes
+// (4 stages): 12288 x 4096, 2048 tokens, 786 -> 525 us (262 -> 393 TFLOP/s
+// of the product), 5120 x 5120, 48 tokens, 56.9 -> 43.8 us; against the
+// general kernel with groups of 64, 3 stages, 4096 x 4096, 1000 tokens, 508
+// -> 105 us.
+//
+// Tried and not kept: 32 x 32 x 16 MFMAs with two of a SIMD's waves in
+// alternate vector and matrix phases (562 us on the first of these, no room
+// for the quarters' running sums); the same phases with this tile, 64 inputs
+// per step (638 us: twice the barriers and per-step work); operand building
+// laid between the MFMAs of one wave by hand (822 us: one token tile in
+// flight).
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "rrq_dma.h"
+#include "rrq_launch.h"
+
+namespace rrq_detail {
+namespace {
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kZpSymmetric = 2;
+constexpr int kScaleF32 = 0, kScaleF16 = 1;
+constexpr uint32_t kHeadroom = 4;   // bits above a quarter's first maximum
+
+__device__ __forceinline__ f32x4 mfma(const u32x4 &a, const u32x4 &b, const f32x4 &c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
+                                                  __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+
+// fma(s, half of q, c) with the low / high binary16 of q (subnormals kept).
+__device__ __forceinline__ float fma_lo(float s, uint32_t q, float c)
+{
+    float d;
+    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel_hi:[0,1,0]" : "=v"(d) : "v"(s), "v"(q), "v"(c));
+    return d;
+}
+__device__ __forceinline__ float fma_hi(float s, uint32_t q, float c)
+{
+    float d;
+    asm("v_fma_mix_f32 %0, %1, %2, %3 op_sel:[0,1,0] op_sel_hi:[0,1,0]"
+        : "=v"(d) : "v"(s), "v"(q), "v"(c));
+    return d;
+}
+
+// The binary16 pair of (a, b), rounded toward zero.
+__device__ __forceinline__ uint32_t pack_pair(float a, float b)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
+}
+
+// hi = the binary16 pair of (a, b), lo = that of what hi leaves (exact
+// differences). v_fma_mixlo / mixhi would write lo directly but issue at half
+// the rate of the three instructions used here.
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t &hi, uint32_t &lo)
+{
+    hi = pack_pair(a, b);
+    float ra, rb;
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[0,0,1]" : "=v"(ra) : "v"(a), "v"(hi));
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
+        : "=v"(rb) : "v"(b), "v"(hi));
+    lo = pack_pair(ra, rb);
+}
+
+__device__ __forceinline__ float pow2(int field)   // 2^(field - 127), 0 below
+{
+    return __uint_as_float((uint32_t)(field > 0 ? field : 0) << 23);
+}
+
+// A running bound (exponent field of a power of two that no value of the
+// chunk reaches twice) and the largest one of the quarter so far. A chunk
+// whose largest exponent field is e raises it when e passes it and lowers it
+// when e lies more than 12 bits below: kHeadroom bits above e within the
+// finite range, at least `least` (the scales then stay representable) and at
+// most 36 bits under the quarter's largest (two such factors leave the
+// accumulators, under 2^47 otherwise, finite). Values thus keep at least 2^-27
+// of their chunk's largest.
+struct Bound {
+    uint32_t at, peak;
+    __device__ __forceinline__ void update(uint32_t e, uint32_t least, bool fresh)
+    {
+        uint32_t b = e + kHeadroom;
+        b = b < 254u ? b : 254u;
+        b = b > e ? b : e;
+        b = b > least ? b : least;
+        const uint32_t low = b + 36u > peak ? b : peak - 36u;
+        if (fresh) at = peak = b;
+        else if (e > at) at = b;
+        else if (e + 12u < at && low < at) at = low;
+        peak = peak > at ? peak : at;
+    }
+};
+
+// A workgroup of WR x WQ waves owns 16 T tokens x 16 WR output rows: wave
+// (wr, wq) rows 16 wr .. 16 wr + 15 for all the tokens, over every quarter of
+// the chunks (WQ = 1) or over quarter wq (WQ = 4).
+template <int K, int GPC, int WR, int WQ, int T>
+struct Tile {
+    static_assert(WQ == 1 || WQ == 4, "all quarters in turn, or one per wave");
+    static_assert(T % WR == 0 || T < WR, "token tiles are prepared by the row waves");
+    static constexpr int TOK = 16 * T;
+    static constexpr int PT = T > WR ? T / WR : 1;           // token tiles a wave prepares
+    static constexpr int X_DMA = 4 * PT;                     // 1 KiB loads per chunk
+    // a wave's share of the package for one chunk: codes (stage t at 512 t,
+    // row-major 16 x 32 bytes), scales and zero-points as 32-bit words
+    // [stage][row][group of the chunk]
+    static constexpr int CODE_DMA = (K + 1) / 2;
+    static constexpr int PARAM_DMA = (K * 16 * GPC + 63) / 64;
+    static constexpr int SCALES = CODE_DMA * 1024;
+    static constexpr int ZEROS = SCALES + PARAM_DMA * 256;
+    static constexpr int W_BYTES = ZEROS + PARAM_DMA * 256;
+    static constexpr int W_DMA = CODE_DMA + 2 * PARAM_DMA;
+    // per buffer and quarter: the activations of one chunk, then per token
+    // the bound's power of two and the factor to it from the last one, then
+    // per tile whether any factor is not 1
+    static constexpr int FX = TOK * 256;
+    static constexpr int RX = FX + TOK * 4;
+    static constexpr int FLAG = RX + TOK * 4;
+    static constexpr int XB = FLAG + ((T * 4 + 15) / 16) * 16;
+    static constexpr int W_BASE = 2 * WQ * XB;
+    static constexpr int BYTES = W_BASE + WR * WQ * W_BYTES;
+    static_assert(BYTES <= 160 * 1024, "LDS of a compute unit");
+    static_assert(X_DMA + W_DMA <= 63, "vmcnt");
+    static_assert(WQ == 1 || WR * WQ * T * 1024 <= W_BASE, "quarters meet in the X buffers");
+};
+
+template <int K, int GPC, int WR, int WQ, int T>
+__global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kernel(
+    const uint32_t *__restrict__ codes, const char *__restrict__ scales,
+    const float *__restrict__ zeros, int64_t rows, int64_t cols, int64_t plane_words,
+    int64_t plane_groups, const uint16_t *__restrict__ X, int64_t n_tokens,
+    float *__restrict__ Y, int zero_point, int scale_type, int row_tiles)
+{
+    using L = Tile<K, GPC, WR, WQ, T>;
+    constexpr int G = 128 / GPC;
+    __shared__ __attribute__((aligned(16))) char smem[L::BYTES];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr = wave % WR, wq = wave / WR;
+    const int n = lane & 15;            // A row (token of a tile), B column (row)
+    const int j = lane >> 4;            // k-slice
+    const bool sym = zero_point == kZpSymmetric;
+
+    const int64_t m0 = (int64_t)(blockIdx.x / row_tiles) * L::TOK;
+    const int64_t o0 = (int64_t)(blockIdx.x % row_tiles) * (16 * WR) + 16 * wr;
+    const uint32_t tokens_here = (uint32_t)(n_tokens - m0 < L::TOK ? n_tokens - m0 : L::TOK);
+    const int64_t rem = rows - o0;
+    const uint32_t rows_here = rem <= 0 ? 0u : (uint32_t)(rem < 16 ? rem : 16);
+    const uint32_t gpr = (uint32_t)(cols / G);
+    const uint32_t row_bytes = (uint32_t)(cols / 4);
+    const uint32_t x_row = (uint32_t)cols * 2;
+    const uint32_t sbytes = scale_type == kScaleF32 ? 4 : 2;
+    const uint32_t code_plane = (uint32_t)plane_words * 4;
+    const uint32_t scale_plane = (uint32_t)plane_groups * sbytes;
+    const uint32_t zero_plane = (uint32_t)plane_groups * 4;
+    const int64_t o_first = rows_here ? o0 : 0;         // rows past the end read nothing
+    const u32x4 dx = make_desc(X + m0 * cols, tokens_here * x_row);
+    const u32x4 dc = make_desc(codes + o_first * (cols / 16),
+                               rows_here ? (K - 1) * code_plane + rows_here * row_bytes : 0u);
+    const u32x4 ds = make_desc(scales + o_first * gpr * sbytes,
+                               rows_here ? (K - 1) * scale_plane + rows_here * gpr * sbytes : 0u);
+    const u32x4 dz = make_desc(sym ? nullptr : zeros + o_first * gpr,
+                               sym || !rows_here ? 0u : (K - 1) * zero_plane + rows_here * gpr * 4);
+
+    const uint32_t chunks = (uint32_t)((cols + 127) / 128);
+    const uint32_t per_q = (chunks + 3) / 4;
+    // this wave's chunks: c_begin .. c_end - 1
+    const uint32_t c_begin = WQ == 1 ? 0u : (per_q * wq < chunks ? per_q * wq : chunks);
+    const uint32_t c_end = WQ == 1 ? chunks : (c_begin + per_q < chunks ? c_begin + per_q : chunks);
+    const uint32_t steps = WQ == 1 ? chunks : per_q;
+
+    // Activations: this wave stages and prepares token tiles t0 .. t0 + PT - 1
+    // (none where the tiles are fewer than the waves). Slot s of a tile holds
+    // token s / 16's piece (s % 16) ^ (token % 16); load i of a tile fills
+    // tokens 4 i .. 4 i + 3. Tokens past the last lie past the descriptor and
+    // read zeros.
+    const int t0 = L::PT * wr;
+    const bool stages_x = T >= WR || t0 < T;
+    uint32_t dma_x[4], x_in[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t tok = (uint32_t)(4 * i + (lane >> 4));
+        x_in[i] = 8u * ((uint32_t)n ^ tok);       // first input of the piece
+        dma_x[i] = ((uint32_t)(16 * t0) + tok) * x_row + 2 * x_in[i];
+    }
+    // Codes: lane l fills bytes 16 (l % 2) of row (l % 32) / 2 in stage
+    // 2 i + l / 32 (a stage past K - 1 is never used).
+    const uint32_t dma_code = (uint32_t)((lane & 31) >> 1) * row_bytes + 16 * (uint32_t)(lane & 1) +
+                              (uint32_t)(lane >> 5) * code_plane;
+    uint32_t dma_par[L::PARAM_DMA], par_st[L::PARAM_DMA];
+#pragma unroll
+    for (int i = 0; i < L::PARAM_DMA; ++i) {
+        const uint32_t s = (uint32_t)(i * 64 + lane);
+        par_st[i] = s / (GPC * 16);
+        dma_par[i] = ((s / GPC) % 16) * gpr + s % GPC;
+    }
+    const uint32_t lds0 = lds_address(&smem[0]);
+    const uint32_t lds_w = lds0 + (uint32_t)(L::W_BASE + wave * L::W_BYTES);
+    const char *my_w = smem + L::W_BASE + wave * L::W_BYTES;
+    auto xbuf = [&](int b) { return smem + (b * WQ + wq) * L::XB; };
+
+    auto issue_x = [&](uint32_t c, int b) {
+        if (!stages_x) return;
+        const uint32_t lds = lds0 + (uint32_t)(b * WQ + wq) * L::XB + (uint32_t)t0 * 4096;
+#pragma unroll
+        for (int i = 0; i < L::X_DMA; ++i) {
+            uint32_t off = dma_x[i % 4];
+            if (GPC > 1 && c * 128 + x_in[i % 4] >= (uint32_t)cols) off = kSkip;
+            dma_x4(dx, c * 256 + (uint32_t)(i / 4) * 16 * x_row, lds + (uint32_t)i * 1024, off);
+        }
+    };
+    auto issue_w = [&](uint32_t c) {
+#pragma unroll
+        for (int i = 0; i < L::CODE_DMA; ++i)
+            dma_x4(dc, c * 32 + 2u * i * code_plane, lds_w + 1024u * i, dma_code);
+#pragma unroll
+        for (int i = 0; i < L::PARAM_DMA; ++i) {
+            const bool in = par_st[i] < (uint32_t)K &&
+                            (GPC == 1 || c * GPC + (uint32_t)(lane % GPC) < gpr);
+            if (scale_type == kScaleF32)
+                dma_dword(ds, c * (GPC * 4), lds_w + L::SCALES + 256u * i,
+                          in ? dma_par[i] * 4 + par_st[i] * scale_plane : kSkip);
+            else
+                dma_ushort(ds, c * (GPC * 2), lds_w + L::SCALES + 256u * i,
+                           in ? dma_par[i] * 2 + par_st[i] * scale_plane : kSkip);
+            dma_dword(dz, c * (GPC * 4), lds_w + L::ZEROS + 256u * i,
+                      in ? dma_par[i] * 4 + par_st[i] * zero_plane : kSkip);
+        }
+    };
+
+    // Rewrites this wave's token tiles of buffer b in place as binary16 with
+    // the tokens' bounds so far and publishes the bounds; values outside a
+    // token's range (or a quarter's first chunk) change the bounds first.
+    Bound ex[L::PT];
+#pragma unroll
+    for (int q = 0; q < L::PT; ++q) ex[q] = {14u, 14u};
+    auto prepare = [&](int b, bool fresh) {
+        char *lb = xbuf(b);
+#pragma unroll
+        for (int q = 0; q < L::PT; ++q) {
+            const int tt = t0 + q;
+            char *xt = lb + (16 * tt + n) * 256;
+            u32x4 v[4], h[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                v[i] = *reinterpret_cast<const u32x4 *>(xt + 16 * ((4 * j + i) ^ n));
+            uint32_t m[4] = {0, 0, 0, 0};
+            const float sc = pow2(268 - (int)ex[q].at);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    h[i][p] = pack_pair(__uint_as_float(v[i][p] << 16) * sc,
+                                        __uint_as_float(v[i][p] & 0xFFFF0000u) * sc);
+                    // the pairs' largest magnitudes (a NaN stays one)
+                    asm("v_pk_maximum3_f16 %0, %0, %1, %1 neg_lo:[0,0,1] neg_hi:[0,0,1]"
+                        : "+v"(m[p]) : "v"(h[i][p]));
+                }
+#pragma unroll
+            for (int p = 1; p < 4; ++p)
+                asm("v_pk_maximum3_f16 %0, %0, %1, %1 neg_lo:[0,0,1] neg_hi:[0,0,1]"
+                    : "+v"(m[0]) : "v"(m[p]));
+            const uint32_t ml = m[0] & 0x7FFFu, mh = (m[0] >> 16) & 0x7FFFu;
+            const uint32_t old = ex[q].at, top = ml > mh ? ml : mh;
+            // 2^15, or 2^3 with the lane's 32 inputs not all zeros
+            const bool outside = top >= 0x7800u || (top < 0x4800u && top != 0u);
+            uint32_t any = 0;
+            if (fresh || __ballot(outside) != 0) {
+                u16x2 mv = {0, 0};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int p = 0; p < 4; ++p)
+                        mv = __builtin_elementwise_max(
+                            mv, __builtin_bit_cast(u16x2, v[i][p] & 0x7FFF7FFFu));
+                uint32_t mx = mv.x > mv.y ? mv.x : mv.y;
+                uint32_t o = (uint32_t)__shfl_xor((int)mx, 16);
+                mx = mx > o ? mx : o;
+                o = (uint32_t)__shfl_xor((int)mx, 32);
+                mx = mx > o ? mx : o;
+                if (mx != 0u || fresh) ex[q].update(mx >> 7, 14u, fresh);
+                any = !fresh && __ballot(ex[q].at != old) != 0;
+                const float s1 = pow2(268 - (int)ex[q].at);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int p = 0; p < 4; ++p)
+                        h[i][p] = pack_pair(__uint_as_float(v[i][p] << 16) * s1,
+                                            __uint_as_float(v[i][p] & 0xFFFF0000u) * s1);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                *reinterpret_cast<u32x4 *>(xt + 16 * ((4 * j + i) ^ n)) = h[i];
+            if (lane < 16) {
+                *reinterpret_cast<float *>(lb + L::FX + 4 * (16 * tt + n)) = __uint_as_float(ex[q].at << 23);
+                *reinterpret_cast<float *>(lb + L::RX + 4 * (16 * tt + n)) =
+                    any ? pow2(127 + (int)old - (int)ex[q].at) : 1.0f;
+                *reinterpret_cast<uint32_t *>(lb + L::FLAG + 4 * tt) = any;
+            }
+        }
+    };
+
+    f32x4 acc[T], run[T];
+#pragma unroll
+    for (int q = 0; q < T; ++q) {
+        acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        run[q] = acc[q];
+    }
+
+    // The lane's package words of one chunk: code words 2 j, 2 j + 1 of its
+    // row, scales and zero-points of the group they lie in.
+    u32x2 cw[K];
+    uint32_t sw[K], zw[K];
+    auto read_w = [&]() {
+        const int gi = GPC == 1 ? 0 : j / (4 / GPC);
+#pragma unroll
+        for (int t = 0; t < K; ++t) {
+            cw[t] = *reinterpret_cast<const u32x2 *>(my_w + 512 * t + 32 * n + 8 * j);
+            const int e = 4 * ((16 * t + n) * GPC + gi);
+            sw[t] = *reinterpret_cast<const uint32_t *>(my_w + L::SCALES + e);
+            zw[t] = *reinterpret_cast<const uint32_t *>(my_w + L::ZEROS + e);
+        }
+    };
+    // Scaled stage scales and zero terms of the lane's row for the chunk; if
+    // a row's bound changed, the accumulators are rescaled.
+    Bound ew = {32u, 32u};
+    float sv[K][3], cz = 0.0f;
+    auto params = [&](bool fresh) {
+        float s[K], z[K], M = 0.0f;
+#pragma unroll
+        for (int t = 0; t < K; ++t) {
+            s[t] = scale_type == kScaleF32 ? __uint_as_float(sw[t])
+                   : scale_type == kScaleF16
+                       ? (float)__builtin_bit_cast(_Float16, (uint16_t)(sw[t] & 0xFFFFu))
+                       : __uint_as_float(sw[t] << 16);
+            z[t] = sym ? 2.0f : __uint_as_float(zw[t]);
+            M = __builtin_fmaf(fabsf(s[t]), 3.0f + fabsf(z[t]), M);
+        }
+        uint32_t e = (__float_as_uint(M) >> 23) & 0xFFu;
+        if constexpr (GPC >= 2) {
+            const uint32_t o = (uint32_t)__shfl_xor((int)e, 32);
+            e = e > o ? e : o;
+        }
+        if constexpr (GPC >= 4) {
+            const uint32_t o = (uint32_t)__shfl_xor((int)e, 16);
+            e = e > o ? e : o;
+        }
+        const uint32_t old = ew.at;
+        if (e != 0u || fresh) ew.update(e, 32u, fresh);
+        if (__ballot(!fresh && ew.at != old) != 0) {
+            const float f = pow2(127 + (int)old - (int)ew.at);
+#pragma unroll
+            for (int q = 0; q < T; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[q][i] *= f;
+        }
+        const float fs = pow2(268 - (int)ew.at);
+        float c = 0.0f;
+#pragma unroll
+        for (int t = 0; t < K; ++t) {
+            const float ss = s[t] * fs;
+            c = __builtin_fmaf(-ss, z[t], c);
+            sv[t][0] = ss * 0x1p20f;
+            sv[t][1] = ss * 0x1p18f;
+            sv[t][2] = ss * 0x1p16f;
+        }
+        cz = c;
+    };
+
+    // B operands of blocks 2 h, 2 h + 1 from the lane's code word h.
+    u32x4 bh[2], bl[2];
+    auto dequant = [&](int h) {
+        float w[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) w[e] = cz;
+#pragma unroll
+        for (int t = 0; t < K; ++t) {
+            const uint32_t c = cw[t][h];
+            const uint32_t up = c << 4, dn = c >> 6;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t src = e < 2 ? up : e < 5 ? c : dn;
+                const int v = e < 2 ? e : e < 5 ? e - 2 : e - 5;
+                const uint32_t q = src & (0x00300030u << (2 * v));
+                w[e] = fma_lo(sv[t][v], q, w[e]);
+                w[e + 8] = fma_hi(sv[t][v], q, w[e + 8]);
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                uint32_t hi, lo;
+                split_pair(w[8 * b + 2 * v], w[8 * b + 2 * v + 1], hi, lo);
+                bh[b][v] = hi;
+                bl[b][v] = lo;
+            }
+    };
+
+    uint32_t q_left = per_q;            // chunks left in the quarter
+    if (c_begin < c_end) {
+        issue_w(c_begin);
+        if (stages_x) {
+            issue_x(c_begin, 0);
+            wait_vm<0>();
+            prepare(0, true);
+        }
+    }
+    for (uint32_t it = 0; it < steps; ++it) {
+        const uint32_t c = c_begin + it;
+        const int b = (int)(it & 1);
+        // every wave has prepared its tiles of this chunk, and is done with
+        // the other buffer
+        __syncthreads();
+        if (c >= c_end) continue;
+        const bool first = q_left == per_q;
+        const bool last = q_left == 1 || c + 1 == c_end;   // of the quarter
+        wait_vm<0>();                   // the package words have landed
+        read_w();
+        const char *lb = xbuf(b);
+        u32x4 flags[(T + 3) / 4];
+#pragma unroll
+        for (int q = 0; q < (T + 3) / 4; ++q)
+            flags[q] = *reinterpret_cast<const u32x4 *>(lb + L::FLAG + 16 * q);
+        if (!first) {
+            uint32_t changed = 0;
+#pragma unroll
+            for (int q = 0; q < T; ++q) changed |= flags[q / 4][q % 4];
+            if (__builtin_amdgcn_readfirstlane(changed)) {
+                // tokens whose bound changed
+#pragma unroll
+                for (int q = 0; q < T; ++q) {
+                    const f32x4 f = *reinterpret_cast<const f32x4 *>(lb + L::RX + 4 * (16 * q + 4 * j));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[q][i] *= f[i];
+                }
+            }
+        }
+        params(first);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            dequant(h);
+            // The next chunk's loads go out between the products (its package
+            // words into this one's place, which has been read). Loads past
+            // the last chunk read other data or zeros, never used.
+            if (h == 0) {
+                issue_x(c + 1, b ^ 1);
+            } else {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                issue_w(c + 1);
+            }
+#pragma unroll
+            for (int q = 0; q < T; ++q) {
+                const char *xt = lb + (16 * q + n) * 256;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const u32x4 a = *reinterpret_cast<const u32x4 *>(xt + 16 * ((4 * j + 2 * h + i) ^ n));
+                    acc[q] = mfma(a, bl[i], acc[q]);
+                    acc[q] = mfma(a, bh[i], acc[q]);
+                }
+            }
+        }
+        --q_left;
+        if (last) {
+            // end of the quarter: fold it into the running sum
+            const float fw = pow2((int)ew.at - 28);
+#pragma unroll
+            for (int q = 0; q < T; ++q) {
+                const f32x4 fx = *reinterpret_cast<const f32x4 *>(lb + L::FX + 4 * (16 * q + 4 * j));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) run[q][i] = run[q][i] + (acc[q][i] * fw) * fx[i];
+                acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            }
+            q_left = per_q;
+        }
+        if (stages_x) {
+            wait_vm<L::W_DMA>();        // the next chunk's activations have landed
+            prepare(b ^ 1, last);
+        }
+    }
+    // no load may still write this workgroup's LDS once it ends or reuses it
+    wait_vm<0>();
+
+    if constexpr (WQ > 1) {
+        // the quarters meet in LDS: tile q of wave v at (v T + q) KiB
+        __syncthreads();
+        f32x4 *red = reinterpret_cast<f32x4 *>(smem);
+        if (wq > 0) {
+#pragma unroll
+            for (int q = 0; q < T; ++q) red[(wave * T + q) * 64 + lane] = run[q];
+        }
+        __syncthreads();
+        if (wq > 0) return;
+#pragma unroll
+        for (int v = 1; v < WQ; ++v)
+#pragma unroll
+            for (int q = 0; q < T; ++q) {
+                const f32x4 p = red[((v * WR + wr) * T + q) * 64 + lane];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) run[q][i] = run[q][i] + p[i];
+            }
+    }
+    // lane: tokens m0 + 16 q + 4 j + i of output row o0 + n
+    if ((uint32_t)n < rows_here) {
+#pragma unroll
+        for (int q = 0; q < T; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t tk = (uint32_t)(16 * q + 4 * j + i);
+                if (tk < tokens_here) Y[(m0 + tk) * rows + o0 + n] = run[q][i];
+            }
+    }
+}
+
+template <typename... Args>
+hipError_t launch(void (*kernel)(Args...), int grid, int block, hipStream_t stream, Args... args)
+{
+    void *argv[] = {static_cast<void *>(&args)...};
+    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(block),
+                           argv, 0, stream);
+}
+
+struct Call {
+    const uint32_t *codes;
+    const char *scales;
+    const float *zeros;
+    int64_t rows, cols;
+    int k, zp, sdt;
+    const uint16_t *X;
+    int64_t n_tokens;
+    float *Y;
+    hipStream_t stream;
+};
+
+template <int K, int GPC, int WR, int WQ, int T>
+hipError_t launch_t(const Call &c)
+{
+    const int row_tiles = (int)((c.rows + 16 * WR - 1) / (16 * WR));
+    const int grid = (int)((int64_t)row_tiles * ((c.n_tokens + 16 * T - 1) / (16 * T)));
+    return launch(split_kernel<K, GPC, WR, WQ, T>, grid, 64 * WR * WQ, c.stream, c.codes,
+                  c.scales, c.zeros, c.rows, c.cols, c.rows * c.cols / 16,
+                  c.rows * c.cols * GPC / 128, c.X, c.n_tokens, c.Y, c.zp, c.sdt, row_tiles);
+}
+
+template <int GPC, int WR, int WQ, int T>
+hipError_t launch_k(const Call &c)
+{
+    if constexpr (GPC > 1) {   // groups of 128 come with 3 or 4 stages only
+        if (c.k == 1) return launch_t<1, GPC, WR, WQ, T>(c);
+        if (c.k == 2) return launch_t<2, GPC, WR, WQ, T>(c);
+    }
+    switch (c.k) {
+    case 3: return launch_t<3, GPC, WR, WQ, T>(c);
+    case 4: return launch_t<4, GPC, WR, WQ, T>(c);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// Tile shapes: A, B, C stage all quarters in turn (8 row waves, 256 / 128 /
+// 64 tokens), D, E, F give each quarter its own waves (32 rows x 64 tokens,
+// 32 x 32, 64 x 32), for calls with too few tiles to fill the chip. One
+// workgroup runs per compute unit, so a call costs its rounds of workgroups
+// times the shape's time per round. kCost is that time in hundredths of B's:
+// measured at 4096 inputs, 4 stages (groups of 128): 158, 103, 75, 34, 25.5,
+// 37 us (158, 100, 69, 33, 24, 35 us at 3 stages and groups of 64).
+enum Shape { A, B, C, D, E, F, kShapes };
+constexpr int kRows[kShapes] = {128, 128, 128, 32, 32, 64};
+constexpr int kTokens[kShapes] = {256, 128, 64, 64, 32, 32};
+constexpr int kCost[kShapes] = {154, 100, 71, 33, 24, 36};
+
+// The cheapest shape and its cost (per 4096 inputs). A and D's buffers do not
+// fit the LDS with groups of 32.
+Shape cheapest(int64_t rows, int64_t n_tokens, int G, int cus, int64_t *cost)
+{
+    Shape best = B;
+    *cost = INT64_MAX;
+    for (int s = kShapes - 1; s >= 0; --s) {
+        if (G == 32 && (s == A || s == D)) continue;
+        const int64_t tiles = ((rows + kRows[s] - 1) / kRows[s]) *
+                              ((n_tokens + kTokens[s] - 1) / kTokens[s]);
+        const int64_t c = (tiles + cus - 1) / cus * kCost[s];
+        if (c < *cost) {
+            *cost = c;
+            best = (Shape)s;
+        }
+    }
+    return best;
+}
+
+template <int GPC>
+hipError_t launch_g(const Call &c, Shape s)
+{
+    switch (s) {
+    case B: return launch_k<GPC, 8, 1, 8>(c);
+    case C: return launch_k<GPC, 8, 1, 4>(c);
+    case E: return launch_k<GPC, 2, 4, 2>(c);
+    case F: return launch_k<GPC, 4, 4, 2>(c);
+    default: break;
+    }
+    if constexpr (GPC < 4) {
+        if (s == A) return launch_k<GPC, 8, 1, 16>(c);
+        if (s == D) return launch_k<GPC, 2, 4, 4>(c);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus)
+{
+    // The activation descriptor spans at most 256 rows of X (under 2^31
+    // bytes), and the grid fits an int.
+    const int64_t tiles32 = ((rows + 31) / 32) * ((n_tokens + 31) / 32);
+    if (n_tokens <= 16 || cols > 65536 || tiles32 >= (1ll << 31)) return false;
+    if (G == 128) {
+        // Below 3 stages the stage products take no more passes than the
+        // split's two and need no operand arithmetic: never ahead there.
+        if (k < 3) return false;
+        // Against the prefill form: ahead once the 128 x 128 tiles (B) give
+        // nearly every compute unit one. 4 / 3 stages: 4096 x 4096, 1024
+        // tokens 114 / 107 against 142 / 110 us, 12288 x 4096, 500 tokens 171
+        // / 160 against 257 / 201, 2048 tokens 529 / 502 against 827 / 656;
+        // with half as many tiles (4096 x 4096, 500 tokens) 86 / 74 against
+        // 86 / 71.
+        if (n_tokens >= kPrefillMinTokens) {
+            const int64_t tiles = ((rows + 127) / 128) * ((n_tokens + 127) / 128);
+            return 8 * tiles >= (k == 4 ? 7 : 8) * (int64_t)cus;
+        }
+    }
+    // Against the general kernel, which takes 16 tokens per pass over the
+    // package with 16 rows per workgroup: its passes cost a fixed part and one
+    // per round of workgroups, here in tenths of the unit of kCost, measured
+    // on 4096 and 12288 rows of 4096 inputs at 17 to 128 tokens.
+    static constexpr int kPerRound[3][4] = {{36, 90, 145, 190}, {18, 40, 61, 80}, {0, 0, 65, 60}};
+    const int64_t passes = (n_tokens + 15) / 16;
+    const int64_t rounds = ((rows + 15) / 16 + cus - 1) / cus;
+    const int per_round = kPerRound[G == 32 ? 0 : G == 64 ? 1 : 2][k - 1];
+    const int64_t general = passes * ((k == 1 ? 45 : 15) + rounds * per_round);
+    int64_t cost;
+    cheapest(rows, n_tokens, G, cus, &cost);
+    return 10 * cost < general;
+}
+
+hipError_t launch_linear_split(const uint32_t *codes, const void *scales, const float *zeros,
+                               int64_t rows, int64_t cols, int G, int k, int zero_point,
+                               int scale_type, const uint16_t *X, int64_t n_tokens, float *Y,
+                               int cus, hipStream_t stream)
+{
+    const Call c = {codes, static_cast<const char *>(scales), zeros, rows, cols, k, zero_point,
+                    scale_type, X, n_tokens, Y, stream};
+    int64_t cost;
+    const Shape shape = cheapest(rows, n_tokens, G, cus, &cost);
+    switch (G) {
+    case 32: return launch_g<4>(c, shape);
+    case 64: return launch_g<2>(c, shape);
+    case 128: return launch_g<1>(c, shape);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace rrq_detail

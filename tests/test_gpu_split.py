@@ -1,0 +1,193 @@
+"""GPU parity of rrq_linear's split form (more than 16 tokens: groups of 32
+and 64, and groups of 128 with 3 or 4 stages), through the C ABI, against the
+oracle's Eq. 20 product in float64.
+
+* exact: power-of-two scales, integer or dyadic zero-points and
+  small-integer activations make every intermediate exactly representable
+  (the weight is a multiple of 2^-4 below 4, so its first binary16 operand
+  holds it), so the sampled outputs must equal the exact value bit for bit:
+  every tile shape, ragged rows, tokens and last chunks, quarters of unequal
+  length and empty ones, every stage count and format;
+* bounded: realistic packages, and scales and activations whose ranges move
+  by many binades along a row (the running bounds rise and fall), stay within
+  the bound of include/rrq.h;
+* the results do not depend on the tile shape a call takes;
+* a token holding an infinity or a NaN does not touch the others.
+Packages come from the oracle or a seeded generator, never from the GPU.
+"""
+
+import math
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from oracle import rrq_oracle as npo
+
+pytestmark = pytest.mark.gpu
+U = 2.0 ** -24
+
+
+def _log(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+def _run(gpu, codes, s_raw, z, rows, cols, G, k, xb, zp="int", sd="f32"):
+    import torch
+    M = xb.size // cols
+    c = torch.from_numpy(codes.view(np.int32).copy()).cuda()
+    sc = torch.from_numpy(s_raw.copy()).cuda()
+    ze = None if z is None else torch.from_numpy(z.copy()).cuda()
+    X = torch.from_numpy(xb.view(np.int16).reshape(M, cols).copy()).cuda().view(torch.bfloat16)
+    Y = torch.full((M, rows), float("nan"), dtype=torch.float32, device="cuda")
+    gpu.rrq_linear_format(c, sc, ze, rows, cols, G, codes.shape[0], gpu.ZERO_POINTS[zp],
+                          gpu.SCALE_TYPES[sd], k, X, M, Y)
+    torch.cuda.synchronize()
+    return Y.cpu().numpy()
+
+
+def _exact(rows, cols, G, M, seed):
+    rng = np.random.default_rng(seed)
+    codes = rng.integers(0, 2 ** 32, (4, rows * cols // 16), dtype=np.uint64).astype(np.uint32)
+    s = (2.0 ** rng.integers(-4, -1, (4, rows * cols // G))).astype(np.float32)
+    z = rng.integers(0, 4, (4, rows * cols // G)).astype(np.float32)
+    xb = npo.f32_to_bf16_bits(rng.integers(-4, 5, (M, cols)).astype(np.float32))
+    return codes, s, z, xb
+
+
+def _sample(rows, seed):
+    if rows <= 320:
+        return np.arange(rows)
+    rng = np.random.default_rng(seed)
+    return np.unique(np.concatenate([np.arange(32), np.arange(rows - 32, rows),
+                                     rng.choice(rows, 96, replace=False)]))
+
+
+# On 256 compute units: 256-, 128- and 64-token tiles of 128 rows for 4090
+# rows at 2043, 1021 and 490 tokens, a quarter per wave with 64-, 32- and
+# 32-token tiles of 32, 32 and 64 rows for 4090 rows at 121 tokens (groups of
+# 64), 250 rows, and 4090 rows at 121 tokens (groups of 32). Rows of 1 to 9
+# chunks of 128 inputs, partial last chunks with the smaller groups.
+@pytest.mark.parametrize("rows,cols,G,M", [
+    (4090, 320, 64, 2043), (4090, 448, 64, 1021), (4090, 64, 64, 490), (4090, 576, 64, 121),
+    (250, 1088, 64, 140), (4090, 608, 32, 1021), (4090, 32, 32, 490), (4090, 1120, 32, 121),
+    (35, 96, 32, 67), (1, 32, 32, 130), (4090, 384, 128, 2043), (4090, 1152, 128, 1021),
+    (4090, 128, 128, 1021), (1023, 640, 128, 127), (70, 128, 128, 66),
+])
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+def test_split_exact(gpu, rows, cols, G, M, k):
+    if G == 128 and k < 3:
+        pytest.skip("groups of 128 take the split form from 3 stages")
+    _log(f"split exact rows={rows} cols={cols} G={G} M={M} k={k}")
+    codes, s, z, xb = _exact(rows, cols, G, M, rows + cols + M + k)
+    y = _run(gpu, codes, s, z, rows, cols, G, k, xb)
+    idx = _sample(rows, cols)
+    ref = npo.linear(codes, s, z, rows, cols, G, k, xb, row_index=idx)
+    bad = np.argwhere(y[:, idx].astype(np.float64) != ref)
+    assert bad.size == 0, f"{len(bad)} outputs differ, first {bad[:3]}"
+    assert not np.any(np.isnan(y)), "unwritten outputs"
+
+
+@pytest.mark.parametrize("zp,sd", [("sym", "f16"), ("real", "f32"), ("int", "bf16"), ("sym", "f32")])
+@pytest.mark.parametrize("rows,cols,G,M,k", [(310, 416, 32, 70, 2), (310, 704, 64, 140, 4),
+                                             (4090, 192, 64, 500, 3), (310, 640, 128, 70, 4)])
+def test_split_exact_formats(gpu, zp, sd, rows, cols, G, M, k):
+    _log(f"split exact format {zp}/{sd} rows={rows} cols={cols} G={G} M={M}")
+    codes, s, z, xb = _exact(rows, cols, G, M, 17)
+    if zp == "sym":
+        zz, zv = None, np.full_like(s, 2.0)
+    elif zp == "real":
+        zz = (np.random.default_rng(5).integers(0, 13, s.shape) * 0.25).astype(np.float32)
+        zv = zz
+    else:
+        zz = zv = z
+    s_raw = (s.astype(np.float16).view(np.uint16) if sd == "f16"
+             else (s.view(np.uint32) >> 16).astype(np.uint16) if sd == "bf16" else s)
+    y = _run(gpu, codes, s_raw, zz, rows, cols, G, k, xb, zp, sd)
+    idx = _sample(rows, 3)
+    ref = npo.linear(codes, s, zv, rows, cols, G, k, xb, row_index=idx)
+    assert np.array_equal(y[:, idx].astype(np.float64), ref)
+
+
+def _bound(s, z, rows, cols, G, k, xb, idx):
+    x = np.abs(npo.bf16_bits_to_f32(xb).reshape(-1, cols).astype(np.float64))
+    T = x.reshape(x.shape[0], cols // G, G).sum(axis=2)
+    A = sum(T @ (np.abs(s[t].astype(np.float64)) * (11 + np.abs(z[t].astype(np.float64))))
+            .reshape(rows, cols // G)[idx].T for t in range(k))
+    p = cols // G
+    n = k * (min(p, 4 * math.ceil(p / 16)) + 1)
+    return 1.05 * U * A * (G + 2 * n + 24) + 1e-300
+
+
+@pytest.mark.parametrize("rows,cols,G,M", [(300, 2048, 64, 140), (4096, 1024, 64, 500),
+                                           (300, 1536, 32, 40), (300, 2048, 128, 72),
+                                           (2048, 512, 128, 2048)])
+@pytest.mark.parametrize("ranges", ["realistic", "moving"])
+def test_split_within_bound(gpu, rows, cols, G, M, ranges):
+    """moving: the scales of a row's groups and the activations of a token's
+    chunks each wander over 2^+-24, every chunk another power of two, and a
+    token and a chunk are all zeros."""
+    rng = np.random.default_rng(rows + cols + G)
+    w = (rng.standard_normal(rows * cols) * 0.02).astype(np.float32)
+    w = np.where(rng.random(w.size) < 1e-3, w * 20, w).astype(np.float32)
+    codes, s, z = oracle.c_construct(npo.f32_to_bf16_bits(w), G, 4)
+    x = rng.standard_normal((M, cols)).astype(np.float32)
+    if ranges == "moving":
+        chunks = -(-cols // 128)
+        f = 2.0 ** rng.integers(-24, 25, (M, chunks))
+        f[:, chunks // 2] = 0
+        x = (x * np.repeat(f, 128, axis=1)[:, :cols]).astype(np.float32)
+        x[3] = 0
+        g = 2.0 ** rng.integers(-24, 25, (rows, chunks))
+        g = np.repeat(g, 128 // G, axis=1)[:, :cols // G].reshape(-1)
+        s = (s * g[None]).astype(np.float32)
+    xb = npo.f32_to_bf16_bits(x)
+    idx = _sample(rows, 1)
+    for k in (3, 4) if G == 128 else (1, 2, 4):
+        y = _run(gpu, codes, s, z, rows, cols, G, k, xb)
+        ref = npo.linear(codes, s, z, rows, cols, G, k, xb, row_index=idx)
+        tol = _bound(s, z, rows, cols, G, k, xb, idx)
+        err = np.abs(y[:, idx].astype(np.float64) - ref)
+        assert np.all(err <= tol), f"k={k}: {np.max(err / tol)}"
+        _log(f"split {ranges} G={G} M={M} k={k}: max err / bound = {np.max(err / tol):.3g}")
+
+
+@pytest.mark.parametrize("G,k", [(64, 2), (32, 4), (128, 4)])
+def test_split_same_results_in_every_shape(gpu, G, k):
+    """The same token gives the same bits whatever the tile shape: 2048 tokens
+    (the largest tiles that fill the chip), the first 1024 and, in calls of
+    127, the first 254 (a quarter of the row per wave)."""
+    rows, cols = 4096, 1152
+    rng = np.random.default_rng(G)
+    w = (rng.standard_normal(rows * cols) * 0.02).astype(np.float32)
+    codes, s, z = oracle.c_construct(npo.f32_to_bf16_bits(w), G, 4)
+    xb = npo.f32_to_bf16_bits(rng.standard_normal((2048, cols)).astype(np.float32))
+    y = _run(gpu, codes, s, z, rows, cols, G, k, xb)
+    for m0, m1 in ((0, 1024), (0, 127), (127, 254)):
+        part = _run(gpu, codes, s, z, rows, cols, G, k, xb.reshape(2048, cols)[m0:m1].reshape(-1))
+        assert np.array_equal(part.view(np.uint32), y[m0:m1].view(np.uint32)), (m0, m1)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3e38, 1e-38])
+def test_split_extreme_token(gpu, value):
+    """One extreme activation in one token: the other tokens' outputs keep
+    their bits; an infinity or a NaN gives that token non-finite outputs."""
+    rows, cols, G, M, k = 96, 640, 64, 140, 4
+    rng = np.random.default_rng(9)
+    w = (rng.standard_normal(rows * cols) * 0.02).astype(np.float32)
+    codes, s, z = oracle.c_construct(npo.f32_to_bf16_bits(w), G, 4)
+    x = rng.standard_normal((M, cols)).astype(np.float32)
+    plain = _run(gpu, codes, s, z, rows, cols, G, k, npo.f32_to_bf16_bits(x))
+    bits = npo.f32_to_bf16_bits(x).reshape(M, cols).copy()
+    bits[7, 200] = np.float32(value).view(np.uint32) >> 16
+    y = _run(gpu, codes, s, z, rows, cols, G, k, bits.reshape(-1))
+    others = np.arange(M) != 7
+    assert np.array_equal(y[others].view(np.uint32), plain[others].view(np.uint32))
+    if not math.isfinite(value):
+        assert not np.any(np.isfinite(y[7]))
+    else:
+        ref = npo.linear(codes, s, z, rows, cols, G, k, bits.reshape(-1))
+        tol = _bound(s, z, rows, cols, G, k, bits.reshape(-1), np.arange(rows))
+        assert np.all(np.abs(y[7].astype(np.float64) - ref[7]) <= tol[7])
