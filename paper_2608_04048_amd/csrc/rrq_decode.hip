@@ -1,5 +1,7 @@
 // Decode form of the stage-sum linear layer (Eq. 20) for up to 4 tokens (5
-// to 16 on rows of 4096 inputs) and groups of 128: Y[m][o] = sum over stages
+// to 16 on rows of 4096 inputs) and groups of 128, with shapes fixed at
+// compile time for rows of 4096, 8192, 12288 and 16384 inputs and one for
+// rows of any other length (ANY below): Y[m][o] = sum over stages
 // t < K and groups g of
 // s_t,o,g (sum_i x_m,i Q_t,o,i - z_t,o,g sum_i x_m,i), the product
 // rrq_linear.hip computes for any shape, organised here for streaming the
@@ -74,6 +76,12 @@ __device__ __forceinline__ f32x4 mfma(const u32x4 &a, const u32x4 &b, const f32x
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// Entry g of a lane's four C rows.
+__device__ __forceinline__ float diagonal(const f32x4 &c, uint32_t g)
+{
+    return g == 0 ? c[0] : g == 1 ? c[1] : g == 2 ? c[2] : c[3];
+}
+
 // One item's LDS slot (a 4-row tile and a set of 4 groups, all K stages):
 // codes of stage t at 1024 (t / 2) + 512 (t % 2), row-major 4 x 128 bytes;
 // scales and zero-points as 32-bit words, stage t of pair n = 4 row + group
@@ -133,6 +141,39 @@ constexpr int depth_for()
     return d < 16 ? d : 16;
 }
 
+// Rows of other lengths (ANY: any number of groups up to kDecodeAnyMaxCols
+// inputs, up to 4 tokens): as many waves as spread the row's sets evenly
+// (their counts differ by at most one), the LDS sized at launch. A wave holds
+// 1 set up to 12 sets (at most 80 VGPRs: 24 waves per CU), 2 up to 24 (96: 20
+// waves), else up to 4 (128: 16 waves), or 5 (168: 12 waves) at 4 stages,
+// where 4 sets spilled. A workgroup has ceil(sets / that) waves and as many
+// of them share a CU as those limits allow, so the LDS per wave, and with it
+// the ring's depth, does not depend on the row. A last set of fewer than 4
+// groups reads zeros as the missing groups' activations, scales and
+// zero-points. A lane frees each stage's P of its offset (4 + z) Sx before it
+// adds it (the fixed shapes take c Sx off at the end of a tile): as many
+// instructions, and no rounding at the offset's magnitude.
+constexpr int any_sets_per_wave(int sets, int k)
+{
+    return sets <= 12 ? 1 : sets <= 24 ? 2 : k < 4 ? 4 : 5;
+}
+constexpr int any_max_waves(int spw) { return spw == 4 ? 15 : 12; }
+constexpr int any_waves_per_cu(int spw) { return spw == 1 ? 24 : spw == 2 ? 20 : spw == 4 ? 16 : 12; }
+// Waves per SIMD the registers are budgeted for (2 sets, 4 stages and a
+// format other than the default need a few more than 96).
+constexpr int any_budget(int k, int spw, bool def)
+{
+    return spw == 2 && k == 4 && !def ? 4 : any_waves_per_cu(spw) / 4;
+}
+
+template <int K, int SPW>
+constexpr int any_depth()
+{
+    constexpr int lds = 160 * 1024 / any_waves_per_cu(SPW) - red_bytes(1, 1);
+    constexpr int by_lds = lds / ItemSlot<K>::BYTES, by_count = 63 / ItemSlot<K>::DMA;
+    return by_lds < by_count ? by_lds : by_count;
+}
+
 // A operands of one set of 4 groups for the lane (token t, group g, k-slice
 // j) from its 32 inputs 32 j .. 32 j + 31 of group g, as four runs of 8
 // (x[32 j .. +7], [+8 .. +15], [+16 .. +23], [+24 .. +31]): block b = 16-input
@@ -188,8 +229,9 @@ __device__ __forceinline__ void wait_runs(u32x4 (&run)[SPW][4])
 // w SPW .. w SPW + SPW - 1 of its WV SPW sets of 4 groups (so the waves of a
 // workgroup read whole rows together); a batch of up to 8 consecutive tiles
 // is reduced across the waves through LDS. Batches go to workgroups in turn.
-template <int K, int D, int WV, int SPW, int TQ, bool DEF>
-__global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void decode_kernel(
+template <int K, int D, int WV, int SPW, int TQ, bool DEF, bool ANY = false>
+__global__ __launch_bounds__(64 * WV, ANY ? any_budget(K, SPW, DEF)
+                                          : WV * wgs_per_cu(WV, SPW, TQ) / 4) void decode_kernel(
     const uint32_t *__restrict__ codes, const char *__restrict__ scales,
     const float *__restrict__ zeros, int64_t rows, int64_t cols, int64_t plane_words,
     int64_t plane_groups, const uint16_t *__restrict__ X, int n_tokens, float *__restrict__ Y,
@@ -197,11 +239,21 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
 {
     using L = ItemSlot<K>;
     // the waves' item rings
-    __shared__ __attribute__((aligned(16))) char ring[WV][D][L::BYTES];
+    __shared__ __attribute__((aligned(16))) char ring[ANY ? 1 : WV][D][L::BYTES];
     // partial row sums: [buffer][wave][tile of the batch][token][row]
-    __shared__ float red[2][WV][kBatch][16 * TQ];
+    __shared__ float red[2][ANY ? 1 : WV][kBatch][16 * TQ];
+    // (ANY: both for the waves launched, the rings first)
+    extern __shared__ __attribute__((aligned(16))) char any_lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = ANY ? (int)(blockDim.x >> 6) : WV;
+    auto partial = [&](int buf, int w, int tile, int e) -> float & {
+        if constexpr (ANY)
+            return reinterpret_cast<float *>(any_lds + waves * D * L::BYTES)
+                [((buf * waves + w) * kBatch + tile) * 16 * TQ + e];
+        else
+            return red[buf][w][tile][e];
+    };
     const int n = lane & 15;
     const int j = lane >> 4;
     const bool sym = zero_point == kZpSymmetric;
@@ -222,7 +274,10 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
     const u32x4 ds = make_desc(scales, (uint32_t)K * (uint32_t)plane_groups * sbytes);
     const u32x4 dz = make_desc(sym ? nullptr : zeros,
                                sym ? 0u : (uint32_t)K * (uint32_t)plane_groups * 4);
-    const uint32_t set0 = (uint32_t)wave * SPW;
+    // this wave's sets: set0 .. set0 + my_sets - 1
+    const int n_sets = (int)((gpr + 3) / 4);
+    const uint32_t set0 = ANY ? (uint32_t)(wave * n_sets / waves) : (uint32_t)wave * SPW;
+    const int my_sets = ANY ? (wave + 1) * n_sets / waves - (int)set0 : SPW;
 
     // DMA lane offsets within an item. Codes: lane l fills bytes 16 l of a
     // 1 KiB load, i.e. stage 2 i + l / 32, row (l % 32) / 8, bytes
@@ -238,15 +293,17 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
     const uint32_t dma_scale = pst < (uint32_t)K ? pgrp * sbytes : kSkip;
     const uint32_t dma_zero = pst < (uint32_t)K ? pgrp * 4 : kSkip;
 
-    const uint32_t lds_ring = lds_address(&ring[wave][0][0]);
-    const char *my_ring = &ring[wave][0][0];
+    const char *my_ring;
+    if constexpr (ANY) my_ring = any_lds + wave * D * L::BYTES;
+    else my_ring = &ring[wave][0][0];
+    const uint32_t lds_ring = lds_address(my_ring);
 
     const int64_t n_tiles = (rows + 3) / 4;
     const int64_t n_batches = (n_tiles + batch - 1) / batch;
     const int my_batches = blockIdx.x < n_batches
                                ? (int)((n_batches - 1 - blockIdx.x) / gridDim.x + 1) : 0;
     const int my_tiles = my_batches * batch;
-    const int total = my_tiles * SPW;                  // items
+    const int total = my_tiles * my_sets;              // items
 
     // DMA of the items in order, one call per item: item it is tile it / SPW
     // of this workgroup's sequence (batch b, tile t of it: tile
@@ -269,19 +326,21 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
         const uint32_t lds = lds_ring + (uint32_t)is_slot * L::BYTES;
         u32x4 c_src = dc, s_src = ds, z_src = dz;
         if (!live) c_src[2] = s_src[2] = z_src[2] = 0u;
+        uint32_t o_scale = dma_scale, o_zero = dma_zero;
+        if (ANY && set * 4 + ((uint32_t)lane & 3) >= gpr) o_scale = o_zero = kSkip;
         // the reads of the item that used this slot have completed
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
         for (int i = 0; i < L::CODE_DMA; ++i)
             dma_x4(c_src, code_base + 2u * i * plane_bytes, lds + 1024u * i, dma_code);
         if (DEF || scale_type == kScaleF32)
-            dma_dword(s_src, grp_base * 4, lds + L::SCALES, dma_scale);
+            dma_dword(s_src, grp_base * 4, lds + L::SCALES, o_scale);
         else
-            dma_ushort(s_src, grp_base * 2, lds + L::SCALES, dma_scale);
-        dma_dword(z_src, grp_base * 4, lds + L::ZEROS, dma_zero);
+            dma_ushort(s_src, grp_base * 2, lds + L::SCALES, o_scale);
+        dma_dword(z_src, grp_base * 4, lds + L::ZEROS, o_zero);
         ++issued;
         if (++is_slot == D) is_slot = 0;
-        if (++is_set == SPW) {
+        if (++is_set == my_sets) {
             is_set = 0;
             if (++is_tt == batch) {
                 is_tt = 0;
@@ -297,7 +356,7 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
     // sets; operand set u = TQ set + q), then the ring.
     const uint32_t ga = n & 3;
     u32x4 run[SPW * TQ][4];
-    {
+    auto load_runs = [&]() {
         const u32x4 xs = make_desc(X, (uint32_t)n_tokens * (uint32_t)cols * 2);
 #pragma unroll
         for (int s = 0; s < SPW; ++s)
@@ -305,15 +364,29 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
             for (int q = 0; q < TQ; ++q) {
                 const int t = 4 * q + (n >> 2);
                 const uint32_t ta = (uint32_t)(t < n_tokens ? t : n_tokens - 1);
-                const uint32_t gi = ((uint32_t)wave * SPW + s) * 4 + ga;
-                const uint32_t off = ta * (uint32_t)cols * 2 + gi * 256 + 64 * (uint32_t)j;
+                const uint32_t gi = (set0 + s) * 4 + ga;
+                uint32_t off = ta * (uint32_t)cols * 2 + gi * 256 + 64 * (uint32_t)j;
+                if (ANY && (s >= my_sets || gi >= gpr)) off = kSkip;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) run[TQ * s + q][i] = load_run(xs, off + 16 * i);
+                for (int i = 0; i < 4; ++i) {
+                    if constexpr (ANY)
+                        run[TQ * s + q][i] = __builtin_amdgcn_raw_buffer_load_b128(
+                            __builtin_amdgcn_make_buffer_rsrc(
+                                const_cast<uint16_t *>(X), 0,
+                                (int)((uint32_t)n_tokens * (uint32_t)cols * 2), kRsrcWord3),
+                            off + 16 * i, 0, 0);
+                    else
+                        run[TQ * s + q][i] = load_run(xs, off + 16 * i);
+                }
             }
-    }
+    };
+    if constexpr (!ANY) load_runs();
 #pragma unroll
     for (int d = 0; d < D; ++d) issue_next();
-    wait_runs<D * L::DMA>(run);
+    // (ANY: up to 20 runs, loaded behind the ring, which lands with them: the
+    // compiler's own wait costs nothing there)
+    if constexpr (ANY) load_runs();
+    else wait_runs<D * L::DMA>(run);
 
     u32x4 a[SPW * TQ][4];
     float sxd[SPW * TQ];
@@ -327,7 +400,7 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
 #pragma unroll
             for (int b = 0; b < 4; ++b) acc = mfma(a[s][b], ones, acc);
             // the lane's diagonal entry (token j, group gb) is the one used
-            sxd[s] = gb == 0 ? acc[0] : gb == 1 ? acc[1] : gb == 2 ? acc[2] : acc[3];
+            sxd[s] = diagonal(acc, gb);
         }
     }
 
@@ -339,6 +412,7 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
         float c[SPW];
 #pragma unroll
         for (int set = 0; set < SPW; ++set) {
+            if (ANY && set >= my_sets) continue;   // (the wave holds fewer sets)
             // this item's loads have landed; the next D - 1 items' may not
             wait_vm<(D - 1) * L::DMA>();
             const char *slot = my_ring + slot_i * L::BYTES;
@@ -370,11 +444,22 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
                             : __uint_as_float(sw << 16);
                     z = sym ? 2.0f : __uint_as_float(zw);
                 }
+                if constexpr (ANY) {
+                    // the lane's diagonal entry alone, freed of its offset
+                    // (4 + z) Sx before it is scaled and added
 #pragma unroll
-                for (int q = 0; q < TQ; ++q)
+                    for (int q = 0; q < TQ; ++q) {
+                        const float d = diagonal(p[q], gb);
+                        acc[q][0] = __builtin_fmaf(
+                            s, __builtin_fmaf(-(4.0f + z), sxd[TQ * set + q], d), acc[q][0]);
+                    }
+                } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[q][i] = __builtin_fmaf(s, p[q][i], acc[q][i]);
-                c[set] = __builtin_fmaf(s, 4.0f + z, c[set]);
+                    for (int q = 0; q < TQ; ++q)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[q][i] = __builtin_fmaf(s, p[q][i], acc[q][i]);
+                    c[set] = __builtin_fmaf(s, 4.0f + z, c[set]);
+                }
             }
             // the slot is free: refill it with the item D ahead
             issue_next();
@@ -385,13 +470,15 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
         // groups of the lanes n = 4 r .. 4 r + 3, kept for the batch reduction
 #pragma unroll
         for (int q = 0; q < TQ; ++q) {
-            float y = gb == 0 ? acc[q][0] : gb == 1 ? acc[q][1] : gb == 2 ? acc[q][2] : acc[q][3];
+            float y = ANY ? acc[q][0] : diagonal(acc[q], gb);
+            if constexpr (!ANY) {
 #pragma unroll
-            for (int set = 0; set < SPW; ++set) y = __builtin_fmaf(-c[set], sxd[TQ * set + q], y);
+                for (int set = 0; set < SPW; ++set) y = __builtin_fmaf(-c[set], sxd[TQ * set + q], y);
+            }
             // (quad permutations [1 0 3 2] and [2 3 0 1]: lanes n ^ 1, n ^ 2)
             y += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, y), 0xB1, 0xF, 0xF, false));
             y += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, y), 0x4E, 0xF, 0xF, false));
-            if (gb == 0) red[n_red & 1][wave][tt][16 * q + 4 * j + r] = y;
+            if (gb == 0) partial(n_red & 1, wave, tt, 16 * q + 4 * j + r) = y;
         }
         if (tt == batch - 1) {
             // end of the batch: sum the waves' partial sums in wave order
@@ -399,16 +486,18 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
             // later, after a barrier that the summing threads reach only once
             // they have read it.
             __syncthreads();
-            const int tid = threadIdx.x;
-            if (tid < batch * 16 * TQ) {
+            const int step = ANY ? waves * 64 : 64 * WV;
+            for (int tid = threadIdx.x; tid < batch * 16 * TQ; tid += step) {
                 const int tb = tid / (16 * TQ), e = tid % (16 * TQ);   // e = 4 token + row
-                float out = red[n_red & 1][0][tb][e];
+                float out = partial(n_red & 1, 0, tb, e);
 #pragma unroll
-                for (int w = 1; w < WV; ++w) out += red[n_red & 1][w][tb][e];
+                for (int w = 1; w < WV; ++w)
+                    if (!ANY || w < waves) out += partial(n_red & 1, w, tb, e);
                 const int64_t tile = ((int64_t)blockIdx.x + (int64_t)bi * gridDim.x) * batch + tb;
                 const int64_t o = tile * 4 + (e & 3);
                 const int tok = e >> 2;
                 if (tok < n_tokens && o < rows) Y[(int64_t)tok * rows + o] = out;
+                if (!ANY) break;   // the workgroup has a thread for every sum
             }
             ++n_red;
             tt = 0;
@@ -422,11 +511,12 @@ __global__ __launch_bounds__(64 * WV, WV * wgs_per_cu(WV, SPW, TQ) / 4) void dec
 }
 
 template <typename... Args>
-hipError_t launch(void (*kernel)(Args...), int grid, int block, hipStream_t stream, Args... args)
+hipError_t launch(void (*kernel)(Args...), int grid, int block, int lds, hipStream_t stream,
+                  Args... args)
 {
     void *argv[] = {static_cast<void *>(&args)...};
     return hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(block),
-                           argv, 0, stream);
+                           argv, lds, stream);
 }
 
 template <int K, int WV, int SPW, int TQ, bool DEF>
@@ -437,8 +527,8 @@ hipError_t launch_k(const uint32_t *codes, const char *scales, const float *zero
     static_assert(wgs_per_cu(WV, SPW, TQ) * (ring_bytes(WV, SPW, TQ) + red_bytes(WV, TQ)) <=
                       160 * 1024, "the workgroups of a CU share its 160 KiB of LDS");
     constexpr int D = depth_for<K, WV, SPW, TQ>();
-    return launch(decode_kernel<K, D, WV, SPW, TQ, DEF>, grid, 64 * WV, stream, codes, scales,
-                  zeros, rows, cols, rows * cols / 16, rows * cols / 128, X, n_tokens, Y, zp, sdt,
+    return launch(decode_kernel<K, D, WV, SPW, TQ, DEF>, grid, 64 * WV, 0, stream, codes,
+                  scales, zeros, rows, cols, rows * cols / 16, rows * cols / 128, X, n_tokens, Y, zp, sdt,
                   batch);
 }
 
@@ -478,13 +568,64 @@ hipError_t launch_d(const uint32_t *codes, const char *scales, const float *zero
     }
 }
 
+// Rows of other lengths (ANY): the workgroup's waves and the workgroups per CU
+// follow from the row's sets.
+template <int K, int SPW, bool DEF>
+hipError_t launch_any_k(const uint32_t *codes, const char *scales, const float *zeros, int64_t rows,
+                        int64_t cols, int zp, int sdt, const uint16_t *X, int n_tokens, float *Y,
+                        int grid, int waves, int batch, hipStream_t stream)
+{
+    constexpr int D = any_depth<K, SPW>(), W = any_max_waves(SPW);
+    static_assert(D >= 2, "a ring holds at least two items");
+    return launch(decode_kernel<K, D, W, SPW, 1, DEF, true>, grid, 64 * waves,
+                  waves * (D * ItemSlot<K>::BYTES + red_bytes(1, 1)), stream, codes, scales, zeros,
+                  rows, cols, rows * cols / 16, rows * cols / 128, X, n_tokens, Y, zp, sdt, batch);
+}
+
+template <int SPW, bool DEF>
+hipError_t launch_any(const uint32_t *codes, const char *scales, const float *zeros, int64_t rows,
+                      int64_t cols, int k, int zp, int sdt, const uint16_t *X, int n_tokens,
+                      float *Y, int grid, int waves, int batch, hipStream_t stream)
+{
+    // (SPW 4 stands for long rows, which take 5 sets per wave at 4 stages)
+    constexpr int SPW4 = SPW == 4 ? 5 : SPW;
+    switch (k) {
+    case 2: return launch_any_k<2, SPW, DEF>(codes, scales, zeros, rows, cols, zp, sdt, X, n_tokens, Y, grid, waves, batch, stream);
+    case 3: return launch_any_k<3, SPW, DEF>(codes, scales, zeros, rows, cols, zp, sdt, X, n_tokens, Y, grid, waves, batch, stream);
+    case 4: return launch_any_k<4, SPW4, DEF>(codes, scales, zeros, rows, cols, zp, sdt, X, n_tokens, Y, grid, waves, batch, stream);
+    default: return hipErrorInvalidValue;   // one stage: linear_decode_fits
+    }
+}
+
+// Rows the kernel has compile-time shapes for.
+bool fixed_shape(int64_t cols) { return cols % 4096 == 0 && cols <= kDecodeMaxCols; }
+
 }  // namespace
 
 bool linear_decode_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens)
 {
-    if (G != 128 || n_tokens < 1 || n_tokens > 16 || cols % 4096 != 0 ||
-        cols > kDecodeMaxCols)
-        return false;
+    if (G != 128 || n_tokens < 1 || n_tokens > 16) return false;
+    if (!fixed_shape(cols)) {
+        // (the last code load of a set may address one stage plane past the
+        // prefix: its offsets stay within 32 bits)
+        if (k < 2 || n_tokens > 4 || cols > kDecodeAnyMaxCols ||
+            (k + 1) * (rows * cols / 4) >= (1ll << 32))
+            return false;
+        // Against the general kernel (packages read from HBM), whose
+        // workgroups of 16 rows run one per compute unit: from its second
+        // round on, i.e. above 4096 rows, ahead at every row length from 2
+        // stages (5120 x 25600, 2 / 4 stages: 46.8 / 93.7 -> 28.6 / 46.5 us;
+        // 25600 x 5120: 42.0 / 75.0 -> 25.9 / 43.1; 25600 x 128, 4 stages:
+        // 15.7 -> 7.5). In one round the general kernel is as fast on short
+        // rows (2048 x 640, 4 / 3 stages: 4.2 / 3.75 against 4.4 / 4.2) and
+        // at 2 stages on rows of moderate length (4096 x 10240: 13.0 against
+        // 16.5; 2000 x 12800: 12.2 against 12.6), unless the rows are few
+        // (1000 x 7680: 8.0 -> 6.2). One stage: behind or even (4096 x 7680:
+        // 6.5 against 13.0; 25600 x 5120: 19.4 against 19.8).
+        if (rows > 4096) return true;
+        if (k >= 3) return cols > 1024;
+        return cols > 12800 || (rows <= 1024 && cols > 4096);
+    }
     // 5 to 8 tokens (two quads, rows of 4096 inputs): measured against the
     // batch form and the general kernel at 5 and 8 tokens, ahead up to 1024
     // rows at every stage count (5.9 against 9.8 us at 4 stages, 8 tokens),
@@ -523,9 +664,12 @@ hipError_t launch_linear_decode(const uint32_t *codes, const void *scales, const
     const char *sc = static_cast<const char *>(scales);
     // Batches of up to 8 tiles, sized so that every resident workgroup
     // gets the same number of batches: R rounds of one batch per workgroup.
-    const int sets = (int)(cols / 512), tq = n_tokens > 8 ? 4 : n_tokens > 4 ? 2 : 1;
-    const int64_t slots = (int64_t)cus * (tq > 1 ? wgs_per_cu(8, 1, tq)
-                                                 : wgs_per_cu(waves_for(sets), sets_per_wave(sets), 1));
+    const bool any = !fixed_shape(cols);
+    const int sets = (int)((cols + 511) / 512), tq = n_tokens > 8 ? 4 : n_tokens > 4 ? 2 : 1;
+    const int any_spw = any_sets_per_wave(sets, k), any_waves = (sets + any_spw - 1) / any_spw;
+    const int64_t slots = (int64_t)cus * (any      ? any_waves_per_cu(any_spw) / any_waves
+                                          : tq > 1 ? wgs_per_cu(8, 1, tq)
+                                                   : wgs_per_cu(waves_for(sets), sets_per_wave(sets), 1));
     const int64_t tiles = (rows + 3) / 4;
     const int64_t rounds = (tiles + slots * kBatch - 1) / (slots * kBatch);
     const int64_t batch = (tiles + slots * rounds - 1) / (slots * rounds);
@@ -533,6 +677,18 @@ hipError_t launch_linear_decode(const uint32_t *codes, const void *scales, const
     const int grid = (int)(batches < slots ? batches : slots);
     const int nt = (int)n_tokens;
     const bool def = scale_type == kScaleF32 && zero_point != kZpSymmetric;
+    if (any) {
+        if (cols > kDecodeAnyMaxCols || n_tokens > 4) return hipErrorInvalidValue;
+        const int w = any_waves, b = (int)batch;
+        if (any_spw == 1)
+            return def ? launch_any<1, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
+                       : launch_any<1, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
+        if (any_spw == 2)
+            return def ? launch_any<2, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
+                       : launch_any<2, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
+        return def ? launch_any<4, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
+                   : launch_any<4, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
+    }
     return def ? launch_d<true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y,
                                 grid, (int)batch, stream)
                : launch_d<false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y,
