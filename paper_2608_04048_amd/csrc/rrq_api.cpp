@@ -161,7 +161,7 @@ int linear_common(const uint32_t *codes, const void *scales, const float *zeros,
     else if (rrq_detail::linear_split_fits(rows, cols, group_size, k_stages, n_tokens, cus))
         e = rrq_detail::launch_linear_split(codes, scales, zeros, rows, cols, group_size, k_stages,
                                             zero_point, scale_type, X, n_tokens, Y, cus, stream);
-    else if (rrq_detail::linear_prefill_fits(rows, cols, group_size, n_tokens))
+    else if (rrq_detail::linear_prefill_fits(rows, cols, group_size, k_stages, n_tokens, cus))
         e = rrq_detail::launch_linear_prefill(codes, scales, zeros, rows, cols, k_stages,
                                               zero_point, scale_type, X, n_tokens, Y, cus,
                                               stream);

@@ -427,10 +427,11 @@ hipError_t launch_k(const uint32_t *codes, const char *scales, const float *zero
 // operand serves 8 token tiles) when it gives at least 3/4 of the compute
 // units a workgroup, else the small one (4 waves, 64 rows x 64 tokens).
 // Measured on 4096 x 4096, 12288 x 4096 and 4096 x 12288 from 256 to 2048
-// tokens, the large tile is the faster one exactly there.
+// tokens, the large tile is the faster one exactly there. Up to 64 tokens it
+// would be half padding.
 bool large_tiles(int64_t rows, int64_t n_tokens, int cus)
 {
-    return 4 * ((rows + 127) / 128) * ((n_tokens + 127) / 128) >= 3 * (int64_t)cus;
+    return n_tokens > 64 && 4 * ((rows + 127) / 128) * ((n_tokens + 127) / 128) >= 3 * (int64_t)cus;
 }
 
 // One stage: waves of 32 rows (8 waves, 256 rows x 128 tokens), so that each
@@ -459,13 +460,35 @@ hipError_t launch_d(const uint32_t *codes, const char *scales, const float *zero
 
 }  // namespace
 
-bool linear_prefill_fits(int64_t rows, int64_t cols, int G, int64_t n_tokens)
+bool linear_prefill_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus)
 {
     // The activation descriptor spans at most 128 rows of X (under 2^31
     // bytes), and the grid (row tiles x token tiles, at most 64 x 64 each)
     // fits an int.
     const int64_t tiles = ((rows + 63) / 64) * ((n_tokens + 63) / 64);
-    return G == 128 && n_tokens >= kPrefillMinTokens && cols <= 65536 && tiles < (1ll << 31);
+    if (G != 128 || n_tokens <= 16 || cols > 65536 || tiles >= (1ll << 31)) return false;
+    if (n_tokens >= kPrefillMinTokens) return true;
+    // Fewer tokens at 1 and 2 stages (from 3 the split form, or the general
+    // kernel where that is ahead of it): the general kernel makes a pass per
+    // 16 tokens, each a round per 16 rows and compute unit, here one or more
+    // rounds of 64 x 64 tiles, two to a compute unit. Both in tenths of a
+    // microsecond per 4096 inputs at 1 / 2 stages: a general round 29 / 51,
+    // the tiles 318 / 378 with one per compute unit, with two 480 / 560 (two
+    // token tiles that share their codes) or 440 / 540 (two row tiles), and
+    // 620 / 760 for 128 x 128 tiles. Measured, general against this form:
+    // 12288 x 4096, 2 stages, 20 / 48 / 64 / 100 tokens 35 / 49 / 62 / 101
+    // against 38 / 38 / 38 / 53 us, 1 stage, 48 / 64 / 100 tokens 28 / 37 / 59
+    // against 32 / 32 / 42; 25600 x 5120, 2 stages, 48 / 100 tokens 132 / 285
+    // against 67 / 98; 5120 x 5120, 2 stages, 48 / 100 tokens 39 / 81 against
+    // 45 / 45; 4096 x 12288, 64 tokens, 60 against 102.
+    if (k > 2) return false;
+    const int64_t passes = (n_tokens + 15) / 16, rounds = ((rows + 15) / 16 + cus - 1) / cus;
+    const int64_t general = passes * rounds * (k == 1 ? 29 : 51);
+    const int64_t here = tiles <= cus              ? (k == 1 ? 318 : 378)
+                         : (rows + 63) / 64 <= cus ? (k == 1 ? 480 : 560)
+                         : n_tokens <= 64          ? (k == 1 ? 440 : 540)
+                                                   : (k == 1 ? 620 : 760);
+    return (tiles + 2 * cus - 1) / (2 * cus) * here < general;
 }
 
 hipError_t launch_linear_prefill(const uint32_t *codes, const void *scales, const float *zeros,
