@@ -1,5 +1,5 @@
-// Decode form of the stage-sum linear layer (Eq. 20) for up to 4 tokens (5
-// to 16 on rows of 4096 inputs) and groups of 128, with shapes fixed at
+// Decode form of the stage-sum linear layer (Eq. 20) for up to 4 tokens (8 on
+// rows of up to 12288 inputs, 16 on rows of 4096) and groups of 128, with shapes fixed at
 // compile time for rows of 4096, 8192, 12288 and 16384 inputs and one for
 // rows of any other length (ANY below): Y[m][o] = sum over stages
 // t < K and groups g of
@@ -142,11 +142,12 @@ constexpr int depth_for()
 }
 
 // Rows of other lengths (ANY: any number of groups up to kDecodeAnyMaxCols
-// inputs, up to 4 tokens): as many waves as spread the row's sets evenly
+// inputs at up to 4 tokens, kDecodeAnyMaxCols8 at 5 to 8): as many waves as spread the row's sets evenly
 // (their counts differ by at most one), the LDS sized at launch. A wave holds
 // 1 set up to 12 sets (at most 80 VGPRs: 24 waves per CU), 2 up to 24 (96: 20
 // waves), else up to 4 (128: 16 waves), or 5 (168: 12 waves) at 4 stages,
-// where 4 sets spilled. A workgroup has ceil(sets / that) waves and as many
+// where 4 sets spilled; with 5 to 8 tokens, whose A operands take twice the
+// registers, 1 (128: 16 waves) or 2 (168: 12 waves). A workgroup has ceil(sets / that) waves and as many
 // of them share a CU as those limits allow, so the LDS per wave, and with it
 // the ring's depth, does not depend on the row. A last set of fewer than 4
 // groups reads zeros as the missing groups' activations, scales and
@@ -158,18 +159,21 @@ constexpr int any_sets_per_wave(int sets, int k)
     return sets <= 12 ? 1 : sets <= 24 ? 2 : k < 4 ? 4 : 5;
 }
 constexpr int any_max_waves(int spw) { return spw == 4 ? 15 : 12; }
-constexpr int any_waves_per_cu(int spw) { return spw == 1 ? 24 : spw == 2 ? 20 : spw == 4 ? 16 : 12; }
+constexpr int any_waves_per_cu(int spw, int tq)
+{
+    return tq > 1 ? (spw == 1 ? 16 : 12) : spw == 1 ? 24 : spw == 2 ? 20 : spw == 4 ? 16 : 12;
+}
 // Waves per SIMD the registers are budgeted for (2 sets, 4 stages and a
 // format other than the default need a few more than 96).
-constexpr int any_budget(int k, int spw, bool def)
+constexpr int any_budget(int k, int spw, int tq, bool def)
 {
-    return spw == 2 && k == 4 && !def ? 4 : any_waves_per_cu(spw) / 4;
+    return tq == 1 && spw == 2 && k == 4 && !def ? 4 : any_waves_per_cu(spw, tq) / 4;
 }
 
-template <int K, int SPW>
+template <int K, int SPW, int TQ>
 constexpr int any_depth()
 {
-    constexpr int lds = 160 * 1024 / any_waves_per_cu(SPW) - red_bytes(1, 1);
+    constexpr int lds = 160 * 1024 / any_waves_per_cu(SPW, TQ) - red_bytes(1, TQ);
     constexpr int by_lds = lds / ItemSlot<K>::BYTES, by_count = 63 / ItemSlot<K>::DMA;
     return by_lds < by_count ? by_lds : by_count;
 }
@@ -230,7 +234,7 @@ __device__ __forceinline__ void wait_runs(u32x4 (&run)[SPW][4])
 // workgroup read whole rows together); a batch of up to 8 consecutive tiles
 // is reduced across the waves through LDS. Batches go to workgroups in turn.
 template <int K, int D, int WV, int SPW, int TQ, bool DEF, bool ANY = false>
-__global__ __launch_bounds__(64 * WV, ANY ? any_budget(K, SPW, DEF)
+__global__ __launch_bounds__(64 * WV, ANY ? any_budget(K, SPW, TQ, DEF)
                                           : WV * wgs_per_cu(WV, SPW, TQ) / 4) void decode_kernel(
     const uint32_t *__restrict__ codes, const char *__restrict__ scales,
     const float *__restrict__ zeros, int64_t rows, int64_t cols, int64_t plane_words,
@@ -570,19 +574,19 @@ hipError_t launch_d(const uint32_t *codes, const char *scales, const float *zero
 
 // Rows of other lengths (ANY): the workgroup's waves and the workgroups per CU
 // follow from the row's sets.
-template <int K, int SPW, bool DEF>
+template <int K, int SPW, int TQ, bool DEF>
 hipError_t launch_any_k(const uint32_t *codes, const char *scales, const float *zeros, int64_t rows,
                         int64_t cols, int zp, int sdt, const uint16_t *X, int n_tokens, float *Y,
                         int grid, int waves, int batch, hipStream_t stream)
 {
-    constexpr int D = any_depth<K, SPW>(), W = any_max_waves(SPW);
+    constexpr int D = any_depth<K, SPW, TQ>(), W = any_max_waves(SPW);
     static_assert(D >= 2, "a ring holds at least two items");
-    return launch(decode_kernel<K, D, W, SPW, 1, DEF, true>, grid, 64 * waves,
-                  waves * (D * ItemSlot<K>::BYTES + red_bytes(1, 1)), stream, codes, scales, zeros,
+    return launch(decode_kernel<K, D, W, SPW, TQ, DEF, true>, grid, 64 * waves,
+                  waves * (D * ItemSlot<K>::BYTES + red_bytes(1, TQ)), stream, codes, scales, zeros,
                   rows, cols, rows * cols / 16, rows * cols / 128, X, n_tokens, Y, zp, sdt, batch);
 }
 
-template <int SPW, bool DEF>
+template <int SPW, int TQ, bool DEF>
 hipError_t launch_any(const uint32_t *codes, const char *scales, const float *zeros, int64_t rows,
                       int64_t cols, int k, int zp, int sdt, const uint16_t *X, int n_tokens,
                       float *Y, int grid, int waves, int batch, hipStream_t stream)
@@ -590,25 +594,28 @@ hipError_t launch_any(const uint32_t *codes, const char *scales, const float *ze
     // (SPW 4 stands for long rows, which take 5 sets per wave at 4 stages)
     constexpr int SPW4 = SPW == 4 ? 5 : SPW;
     switch (k) {
-    case 2: return launch_any_k<2, SPW, DEF>(codes, scales, zeros, rows, cols, zp, sdt, X, n_tokens, Y, grid, waves, batch, stream);
-    case 3: return launch_any_k<3, SPW, DEF>(codes, scales, zeros, rows, cols, zp, sdt, X, n_tokens, Y, grid, waves, batch, stream);
-    case 4: return launch_any_k<4, SPW4, DEF>(codes, scales, zeros, rows, cols, zp, sdt, X, n_tokens, Y, grid, waves, batch, stream);
+    case 2: return launch_any_k<2, SPW, TQ, DEF>(codes, scales, zeros, rows, cols, zp, sdt, X, n_tokens, Y, grid, waves, batch, stream);
+    case 3: return launch_any_k<3, SPW, TQ, DEF>(codes, scales, zeros, rows, cols, zp, sdt, X, n_tokens, Y, grid, waves, batch, stream);
+    case 4: return launch_any_k<4, SPW4, TQ, DEF>(codes, scales, zeros, rows, cols, zp, sdt, X, n_tokens, Y, grid, waves, batch, stream);
     default: return hipErrorInvalidValue;   // one stage: linear_decode_fits
     }
 }
 
 // Rows the kernel has compile-time shapes for.
-bool fixed_shape(int64_t cols) { return cols % 4096 == 0 && cols <= kDecodeMaxCols; }
+bool fixed_shape(int64_t cols, int64_t n_tokens)
+{
+    return cols % 4096 == 0 && (n_tokens > 4 ? cols == 4096 : cols <= kDecodeMaxCols);
+}
 
 }  // namespace
 
 bool linear_decode_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens)
 {
     if (G != 128 || n_tokens < 1 || n_tokens > 16) return false;
-    if (!fixed_shape(cols)) {
+    if (!fixed_shape(cols, n_tokens)) {
         // (the last code load of a set may address one stage plane past the
         // prefix: its offsets stay within 32 bits)
-        if (k < 2 || n_tokens > 4 || cols > kDecodeAnyMaxCols ||
+        if (k < 2 || n_tokens > 8 || cols > (n_tokens > 4 ? kDecodeAnyMaxCols8 : kDecodeAnyMaxCols) ||
             (k + 1) * (rows * cols / 4) >= (1ll << 32))
             return false;
         // Against the general kernel (packages read from HBM), whose
@@ -622,6 +629,14 @@ bool linear_decode_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_toke
         // 16.5; 2000 x 12800: 12.2 against 12.6), unless the rows are few
         // (1000 x 7680: 8.0 -> 6.2). One stage: behind or even (4096 x 7680:
         // 6.5 against 13.0; 25600 x 5120: 19.4 against 19.8).
+        // 5 to 8 tokens, rows of up to 12288 inputs: the line lies in the
+        // same place (8 tokens, 4 / 2 stages: 25600 x 5120 89.5 -> 54.6 us at
+        // 4; 5120 x 5120 26.3 / 16.0 -> 16.0 / 11.5; 1024 x 5120 11.6 / 8.3
+        // -> 7.3 / 6.8; 4096 x 8192 22.0 -> 18.0 at 4, 13.6 against 13.9 at 2;
+        // 2048 x 1024 5.1 against 5.4 at 4), but for the rows the batch form
+        // takes, where that is ahead or even (12288 x 3072: 18.8 / 12.7 against
+        // 20.0 / 14.6).
+        if (n_tokens > 4 && cols >= 2048 && cols <= 4096) return false;
         if (rows > 4096) return true;
         if (k >= 3) return cols > 1024;
         return cols > 12800 || (rows <= 1024 && cols > 4096);
@@ -639,9 +654,8 @@ bool linear_decode_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_toke
     // 3 stages: 9.0 / 8.7 against 10.8 / 9.3 us; 256 rows, 4 stages: 8.2
     // against 9.5); behind at 1 and 2 stages (8.1 against 7.3 us at 2) and
     // even from 2048 rows.
-    if (n_tokens > 8) return cols == 4096 && rows <= 1024 && k >= 3;
+    if (n_tokens > 8) return rows <= 1024 && k >= 3;
     if (n_tokens > 4) {
-        if (cols != 4096) return false;
         return rows <= 1024 || (k >= 3 && (rows <= 2048 || (rows > 4096 && rows <= 6144)));
     }
     // Measured crossover against the general kernel (one token, packages
@@ -660,14 +674,14 @@ hipError_t launch_linear_decode(const uint32_t *codes, const void *scales, const
                                 const uint16_t *X, int64_t n_tokens, float *Y, int cus,
                                 hipStream_t stream)
 {
-    if (n_tokens < 1 || n_tokens > 16 || (n_tokens > 4 && cols != 4096)) return hipErrorInvalidValue;
+    if (n_tokens < 1 || n_tokens > 16) return hipErrorInvalidValue;
     const char *sc = static_cast<const char *>(scales);
     // Batches of up to 8 tiles, sized so that every resident workgroup
     // gets the same number of batches: R rounds of one batch per workgroup.
-    const bool any = !fixed_shape(cols);
+    const bool any = !fixed_shape(cols, n_tokens);
     const int sets = (int)((cols + 511) / 512), tq = n_tokens > 8 ? 4 : n_tokens > 4 ? 2 : 1;
     const int any_spw = any_sets_per_wave(sets, k), any_waves = (sets + any_spw - 1) / any_spw;
-    const int64_t slots = (int64_t)cus * (any      ? any_waves_per_cu(any_spw) / any_waves
+    const int64_t slots = (int64_t)cus * (any      ? any_waves_per_cu(any_spw, tq) / any_waves
                                           : tq > 1 ? wgs_per_cu(8, 1, tq)
                                                    : wgs_per_cu(waves_for(sets), sets_per_wave(sets), 1));
     const int64_t tiles = (rows + 3) / 4;
@@ -678,16 +692,22 @@ hipError_t launch_linear_decode(const uint32_t *codes, const void *scales, const
     const int nt = (int)n_tokens;
     const bool def = scale_type == kScaleF32 && zero_point != kZpSymmetric;
     if (any) {
-        if (cols > kDecodeAnyMaxCols || n_tokens > 4) return hipErrorInvalidValue;
+        if (cols > (tq > 1 ? kDecodeAnyMaxCols8 : kDecodeAnyMaxCols) || tq > 2) return hipErrorInvalidValue;
         const int w = any_waves, b = (int)batch;
+        if (tq > 1 && any_spw == 1)
+            return def ? launch_any<1, 2, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
+                       : launch_any<1, 2, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
+        if (tq > 1)
+            return def ? launch_any<2, 2, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
+                       : launch_any<2, 2, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
         if (any_spw == 1)
-            return def ? launch_any<1, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
-                       : launch_any<1, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
+            return def ? launch_any<1, 1, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
+                       : launch_any<1, 1, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
         if (any_spw == 2)
-            return def ? launch_any<2, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
-                       : launch_any<2, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
-        return def ? launch_any<4, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
-                   : launch_any<4, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
+            return def ? launch_any<2, 1, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
+                       : launch_any<2, 1, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
+        return def ? launch_any<4, 1, true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream)
+                   : launch_any<4, 1, false>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y, grid, w, b, stream);
     }
     return def ? launch_d<true>(codes, sc, zeros, rows, cols, k, zero_point, scale_type, X, nt, Y,
                                 grid, (int)batch, stream)

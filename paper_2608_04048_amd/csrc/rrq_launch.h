@@ -59,13 +59,16 @@ hipError_t launch_linear(const uint32_t *codes, const void *scales, const float 
 
 // The decode form of the linear layer (up to 4 tokens, groups of 128, cols
 // a multiple of 4096 up to kDecodeMaxCols or of any other length up to
-// kDecodeAnyMaxCols, or 5 to 16 tokens on rows of 4096 inputs; and the stage, row and token counts where it is the faster one:
+// kDecodeAnyMaxCols, 5 to 8 tokens on rows of up to kDecodeAnyMaxCols8 inputs,
+// or 9 to 16 on rows of 4096; and the stage, row and token counts where it is the faster one:
 // linear_decode_fits);
 // launch_linear covers every other case.
 constexpr int kDecodeMaxCols = 16384;
 // Rows of other lengths (60 sets of 512 inputs: 12 waves of 5
 // or 15 of 4).
 constexpr int kDecodeAnyMaxCols = 30720;
+// With 5 to 8 tokens (12 waves of 2 sets).
+constexpr int kDecodeAnyMaxCols8 = 12288;
 // The batch form (groups of 128, kBatchMinTokens to 16 tokens, at most 4096
 // cols: the A operands of a wave's groups stay in its registers; and the
 // row, column, stage and token counts where it is the faster one:

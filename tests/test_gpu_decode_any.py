@@ -1,5 +1,5 @@
 """GPU parity of rrq_linear's decode form on rows that are no multiple of 4096
-inputs (up to 4 tokens, groups of 128, up to 30720 inputs) against the
+inputs (groups of 128; up to 4 tokens on up to 30720 inputs, 5 to 8 on up to 12288) against the
 oracle's Eq. 20 product in float64.
 
 * exact: power-of-two scales, integer zero-points and small-integer
@@ -37,6 +37,9 @@ def _package(rows, cols, M, seed):
     (1027, 7680, 1), (259, 10240, 4), (130, 12416, 2), (1024, 20480, 1), (1100, 25600, 1),
     (130, 30592, 3), (67, 30720, 4), (1, 20608, 1),
     # the rule's edges: short rows up to 4096 of them, rows past the longest
+    # 5 to 8 tokens, up to 12288 inputs; their edges
+    (5000, 128, 8), (4097, 640, 5), (1025, 1152, 6), (1024, 5120, 8), (5121, 5888, 7), (516, 6272, 8),
+    (1027, 8192, 5), (1022, 12288, 8), (300, 12416, 6), (1030, 1920, 8), (1030, 2048, 7),
     (4096, 640, 2), (2049, 1024, 1), (2049, 1152, 1), (67, 30848, 2), (1025, 12800, 1),
 ])
 @pytest.mark.parametrize("k", [1, 2, 3, 4])
@@ -52,10 +55,11 @@ def test_decode_any_exact(gpu, rows, cols, M, k):
 
 
 @pytest.mark.parametrize("zp,sd", [("sym", "f16"), ("real", "f32"), ("int", "bf16")])
-@pytest.mark.parametrize("rows,cols,k", [(1022, 1664, 3), (517, 10368, 4), (130, 25600, 2)])
-def test_decode_any_exact_formats(gpu, zp, sd, rows, cols, k):
+@pytest.mark.parametrize("rows,cols,k,M", [(1022, 1664, 3, 3), (517, 10368, 4, 3), (130, 25600, 2, 3),
+                                           (1022, 1664, 4, 7), (517, 10368, 4, 6)])
+def test_decode_any_exact_formats(gpu, zp, sd, rows, cols, k, M):
     _log(f"decode any format {zp}/{sd} rows={rows} cols={cols}")
-    codes, s, z, xb = _package(rows, cols, 3, 5)
+    codes, s, z, xb = _package(rows, cols, M, 5)
     z = None if zp == "sym" else z * 0.25 if zp == "real" else z
     s_raw = (s.astype(np.float16).view(np.uint16) if sd == "f16"
              else (s.view(np.uint32) >> 16).astype(np.uint16) if sd == "bf16" else s)
