@@ -346,7 +346,8 @@ int rrq_reconstruct_format(const uint32_t *codes, const void *scales, const floa
  *              faster (groups of 32 and 64; groups of 128 with 3 or 4
  *              stages, by row and token count) more than 16 tokens take the
  *              split form below, whose results are closer to the exact value
- *              and do not depend on n_tokens within the form.
+ *              and, on rows of up to 8192 inputs, do not depend on n_tokens
+ *              within the form.
  *   Y          device, float [n_tokens][rows], 4-byte aligned (written).
  *   stream     HIP stream the work is enqueued on.
  *

@@ -21,10 +21,12 @@
 // activations with outliers that happens in a few of the first chunks.
 //
 // Accumulation order: the chunks of a row in 4 contiguous quarters
-// (ceil(chunks / 4) each), each accumulated from 0 in chunk order (block by
-// block, lo before hi), and the quarters added in order. The order does not
-// depend on the tile shape or on which waves take the quarters, so every
-// token count gives the same results.
+// (ceil(chunks / 4) each), a quarter in stretches of 16 chunks, each
+// accumulated from 0 in chunk order (block by block, lo before hi), and the
+// stretches added in order. On rows of up to 8192 inputs a quarter is one
+// stretch and the order does not depend on the tile shape or on which waves
+// take the quarters: every token count gives the same results. On longer rows
+// quarters of their own waves are summed before they meet.
 //
 // What bounds it: vector issue. Per chunk of 16 rows a wave forms its B
 // operands with about 330 vector instructions at 4 stages (8 per element)
@@ -64,6 +66,11 @@ typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 constexpr int kZpSymmetric = 2;
 constexpr int kScaleF32 = 0, kScaleF16 = 1;
 constexpr uint32_t kHeadroom = 4;   // bits above a quarter's first maximum
+// Chunks accumulated before they are folded into the running sum: in one
+// stretch, a quarter of a long row loses more in its 16 x 50 accumulations
+// than the stage-sum forms do (25600 inputs, 1 stage, groups of 32: 6.3e-7
+// against 4.5e-7 off 64 bits).
+constexpr uint32_t kFoldChunks = 16;
 
 __device__ __forceinline__ f32x4 mfma(const u32x4 &a, const u32x4 &b, const f32x4 &c)
 {
@@ -505,8 +512,9 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
             }
         }
         --q_left;
-        if (last) {
-            // end of the quarter: fold it into the running sum
+        if (last || (per_q - q_left) % kFoldChunks == 0) {
+            // end of the quarter or of a stretch of it: fold it into the
+            // running sum (the bounds run on within the quarter)
             const float fw = pow2((int)ew.at - 28);
 #pragma unroll
             for (int q = 0; q < T; ++q) {
@@ -515,7 +523,7 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
                 for (int i = 0; i < 4; ++i) run[q][i] = run[q][i] + (acc[q][i] * fw) * fx[i];
                 acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
             }
-            q_left = per_q;
+            if (last) q_left = per_q;
         }
         if (stages_x) {
             wait_vm<L::W_DMA>();        // the next chunk's activations have landed
