@@ -80,7 +80,7 @@ hipError_t launch_linear_batch(const uint32_t *codes, const void *scales, const 
                                const uint16_t *X, int64_t n_tokens, float *Y, int cus,
                                hipStream_t stream);
 // The prefill form (groups of 128, at least kPrefillMinTokens tokens, or
-// more than 16 at 1 and 2 stages where the rows give enough tiles:
+// more than 16 where the rows give enough tiles:
 // linear_prefill_fits;
 // 128-token x 128-row tiles when they still give every compute unit one,
 // else 64 x 64). Measured against the general kernel on the Qwen3-8B shapes:
@@ -96,6 +96,8 @@ hipError_t launch_linear_prefill(const uint32_t *codes, const void *scales, cons
 // token counts where it is the faster one: linear_split_fits): the prefix
 // weight formed in binary32 and split into two binary16 operands, two
 // matrix-core passes whatever the stage count.
+// Its time with groups of 128, in tenths of a microsecond per 4096 inputs.
+int64_t split_cost(int64_t rows, int64_t n_tokens, int cus);
 bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus);
 hipError_t launch_linear_split(const uint32_t *codes, const void *scales, const float *zeros,
                                int64_t rows, int64_t cols, int G, int k, int zero_point,

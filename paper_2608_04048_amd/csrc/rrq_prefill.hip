@@ -468,11 +468,10 @@ bool linear_prefill_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tok
     const int64_t tiles = ((rows + 63) / 64) * ((n_tokens + 63) / 64);
     if (G != 128 || n_tokens <= 16 || cols > 65536 || tiles >= (1ll << 31)) return false;
     if (n_tokens >= kPrefillMinTokens) return true;
-    // Fewer tokens at 1 and 2 stages (from 3 the split form, or the general
-    // kernel where that is ahead of it): the general kernel makes a pass per
+    // Fewer tokens: the general kernel makes a pass per
     // 16 tokens, each a round per 16 rows and compute unit, here one or more
     // rounds of 64 x 64 tiles, two to a compute unit. Both in tenths of a
-    // microsecond per 4096 inputs at 1 / 2 stages: a general round 29 / 51,
+    // microsecond per 4096 inputs, at 1 / 2 stages: a general round 29 / 51,
     // the tiles 318 / 378 with one per compute unit, with two 480 / 560 (two
     // token tiles that share their codes) or 440 / 540 (two row tiles), and
     // 620 / 760 for 128 x 128 tiles. Measured, general against this form:
@@ -481,14 +480,22 @@ bool linear_prefill_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tok
     // against 32 / 32 / 42; 25600 x 5120, 2 stages, 48 / 100 tokens 132 / 285
     // against 67 / 98; 5120 x 5120, 2 stages, 48 / 100 tokens 39 / 81 against
     // 45 / 45; 4096 x 12288, 64 tokens, 60 against 102.
-    if (k > 2) return false;
+    // At 3 / 4 stages the tiles take 446 / 505, 646 / 782, 730 / 1024 and
+    // 1025 / 1426, and the split form's shapes are the other side as well:
+    // 12288 x 4096, 48 / 64 tokens 60 / 66 and 74 / 74 against 45 / 45 and 51 /
+    // 52 us; 5120 x 5120, 64 / 100 tokens, 4 stages, 46 / 86 against 60 / 61;
+    // 4096 x 12288, 120 tokens, 4 stages, 100 against 138.
+    static constexpr int kGeneralRound[4] = {29, 51, 65, 60};
+    static constexpr int kTiles[4][4] = {{318, 378, 446, 505}, {480, 560, 646, 782},
+                                         {440, 540, 730, 1024}, {620, 760, 1025, 1426}};
     const int64_t passes = (n_tokens + 15) / 16, rounds = ((rows + 15) / 16 + cus - 1) / cus;
-    const int64_t general = passes * rounds * (k == 1 ? 29 : 51);
-    const int64_t here = tiles <= cus              ? (k == 1 ? 318 : 378)
-                         : (rows + 63) / 64 <= cus ? (k == 1 ? 480 : 560)
-                         : n_tokens <= 64          ? (k == 1 ? 440 : 540)
-                                                   : (k == 1 ? 620 : 760);
-    return (tiles + 2 * cus - 1) / (2 * cus) * here < general;
+    int64_t other = passes * rounds * kGeneralRound[k - 1];
+    if (k > 2) {
+        const int64_t split = split_cost(rows, n_tokens, cus);
+        other = split < other ? split : other;
+    }
+    const int shape = tiles <= cus ? 0 : (rows + 63) / 64 <= cus ? 1 : n_tokens <= 64 ? 2 : 3;
+    return (tiles + 2 * cus - 1) / (2 * cus) * kTiles[shape][k - 1] < other;
 }
 
 hipError_t launch_linear_prefill(const uint32_t *codes, const void *scales, const float *zeros,

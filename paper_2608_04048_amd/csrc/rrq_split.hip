@@ -658,6 +658,13 @@ hipError_t launch_g(const Call &c, Shape s)
 
 }  // namespace
 
+int64_t split_cost(int64_t rows, int64_t n_tokens, int cus)
+{
+    int64_t cost;
+    cheapest(rows, n_tokens, 128, cus, &cost);
+    return 10 * cost;
+}
+
 bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus)
 {
     // The activation descriptor spans at most 256 rows of X (under 2^31
@@ -665,6 +672,8 @@ bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_token
     const int64_t tiles32 = ((rows + 31) / 32) * ((n_tokens + 31) / 32);
     if (n_tokens <= 16 || cols > 65536 || tiles32 >= (1ll << 31)) return false;
     if (G == 128) {
+        if (n_tokens < kPrefillMinTokens && linear_prefill_fits(rows, cols, G, k, n_tokens, cus))
+            return false;
         // Below 3 stages the stage products take no more passes than the
         // split's two and need no operand arithmetic: never ahead there.
         if (k < 3) return false;

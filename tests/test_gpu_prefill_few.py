@@ -1,5 +1,5 @@
-"""GPU parity of rrq_linear's prefill form with 17 to 127 tokens at 1 and 2
-stages, against the oracle's Eq. 20 product in float64: power-of-two scales,
+"""GPU parity of rrq_linear's prefill form with 17 to 127 tokens
+against the oracle's Eq. 20 product in float64: power-of-two scales,
 integer zero-points and small-integer activations make every intermediate
 exactly representable, so the sampled outputs must equal the exact value bit
 for bit. Shapes on both sides of the rule that picks the form (256 compute
@@ -23,7 +23,7 @@ pytestmark = pytest.mark.gpu
     # the general kernel's side
     (12288, 128, 17), (4096, 384, 64), (300, 1152, 100),
 ])
-@pytest.mark.parametrize("k", [1, 2])
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
 def test_few_tokens_exact(gpu, rows, cols, M, k):
     _log(f"few tokens rows={rows} cols={cols} M={M} k={k}")
     codes, s, z, xb = _package(rows, cols, M, rows + cols + M + k)
