@@ -346,8 +346,9 @@ int rrq_reconstruct_format(const uint32_t *codes, const void *scales, const floa
  *              faster (groups of 32 and 64; groups of 128 with 3 or 4
  *              stages, by row and token count) more than 16 tokens take the
  *              split form below, whose results are closer to the exact value
- *              and, on rows of up to 8192 inputs, do not depend on n_tokens
- *              within the form.
+ *              and, on rows of up to 2048 inputs, do not depend on n_tokens
+ *              within the form (on longer rows its tile shapes differ in the
+ *              last bits).
  *   Y          device, float [n_tokens][rows], 4-byte aligned (written).
  *   stream     HIP stream the work is enqueued on.
  *
@@ -359,15 +360,11 @@ int rrq_reconstruct_format(const uint32_t *codes, const void *scales, const floa
  * (11 + |z_t,g|) sum_{i in g} |X[m][i]|, p = groups per row and
  * n = k_stages * (min(p, 4 ceil(p / 16)) + 1),
  * |Y[m][o] - exact| <= 1.05 u A (group_size + 2 n + 24).
- * The split form forms the prefix weight sum_t s_t (Q_t - z_t) in binary32,
- * splits it into two binary16 operands (to 2^-22 of itself) and takes X to
- * binary16, both scaled by powers of two that follow their ranges along a
- * row, so that a value keeps at least 2^-27 of the largest of its 128 inputs;
- * its error on packages of this library lies about three times below the
- * products' own (2-norm 4e-7 against 1.3e-6 of the result at 4 stages), and
- * the bound above holds where the scales of the groups that share 128 inputs
- * of a row (groups of 32 and 64), and scales and activations along a row,
- * stay within 2^36 of each other.
+ * The bound holds for every form. The split form forms the prefix weight
+ * sum_t s_t (Q_t - z_t) in binary32 and multiplies its 24 bits, cut into three
+ * bfloat16 operands, by X as it is; its error on packages of this library lies
+ * about five times below that of the products of the stages (2-norm 2.6e-7
+ * against 1.3e-6 of the result at 4 stages).
  *
  * Returns RRQ_OK, or RRQ_ERR_NULL / _ALIGN / _SHAPE / _GROUP / _STAGES with
  * nothing enqueued, or RRQ_ERR_HIP if the kernel launch failed.

@@ -94,10 +94,12 @@ hipError_t launch_linear_prefill(const uint32_t *codes, const void *scales, cons
                                  int cus, hipStream_t stream);
 // The split form (more than 16 tokens, any group size; the stage, row and
 // token counts where it is the faster one: linear_split_fits): the prefix
-// weight formed in binary32 and split into two binary16 operands, two
+// weight formed in binary32 and split into three bfloat16 operands, three
 // matrix-core passes whatever the stage count.
-// Its time with groups of 128, in tenths of a microsecond per 4096 inputs.
-int64_t split_cost(int64_t rows, int64_t n_tokens, int cus);
+// Its time and the general kernel's with more than 16 tokens, in tenths of a
+// microsecond per 4096 inputs.
+int64_t split_cost(int64_t rows, int64_t n_tokens, int k, int cus);
+int64_t general_cost(int64_t rows, int64_t n_tokens, int G, int k, int cus);
 bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus);
 hipError_t launch_linear_split(const uint32_t *codes, const void *scales, const float *zeros,
                                int64_t rows, int64_t cols, int G, int k, int zero_point,

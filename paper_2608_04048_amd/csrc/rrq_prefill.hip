@@ -485,13 +485,11 @@ bool linear_prefill_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tok
     // 12288 x 4096, 48 / 64 tokens 60 / 66 and 74 / 74 against 45 / 45 and 51 /
     // 52 us; 5120 x 5120, 64 / 100 tokens, 4 stages, 46 / 86 against 60 / 61;
     // 4096 x 12288, 120 tokens, 4 stages, 100 against 138.
-    static constexpr int kGeneralRound[4] = {29, 51, 65, 60};
     static constexpr int kTiles[4][4] = {{318, 378, 446, 505}, {480, 560, 646, 782},
                                          {440, 540, 730, 1024}, {620, 760, 1025, 1426}};
-    const int64_t passes = (n_tokens + 15) / 16, rounds = ((rows + 15) / 16 + cus - 1) / cus;
-    int64_t other = passes * rounds * kGeneralRound[k - 1];
+    int64_t other = general_cost(rows, n_tokens, G, k, cus);
     if (k > 2) {
-        const int64_t split = split_cost(rows, n_tokens, cus);
+        const int64_t split = split_cost(rows, n_tokens, k, cus);
         other = split < other ? split : other;
     }
     const int shape = tiles <= cus ? 0 : (rows + 63) / 64 <= cus ? 1 : n_tokens <= 64 ? 2 : 3;

@@ -1,52 +1,50 @@
 // Split form of the stage-sum linear layer (Eq. 20) for more than 16 tokens:
 // Y[m][o] = sum_i X[m][i] W~[o][i] with the prefix weight
 // W~ = sum over stages t < K of s_t (Q_t - z_t) formed once per tile in
-// binary32 and split into two binary16 operands, so that a product takes two
-// matrix-core passes whatever the stage count.
+// binary32 and split into three bfloat16 operands, so that a product takes
+// three matrix-core passes whatever the stage count.
 //
-// Operands (v_mfma_f32_16x16x32_f16, lane l: row / column n = l % 16,
+// Operands (v_mfma_f32_16x16x32_bf16, lane l: row / column n = l % 16,
 // k-slice j = l / 16, a chunk = 128 inputs, lane j owning inputs
 // 32 j .. 32 j + 31 of it, block b = inputs 32 j + 8 b .. + 7):
-//   * B: w' = W~ 2^(14 - Ew) in binary32 (Ew a running exponent bound of the
-//     row, see below), hi = f16(w'), lo = f16(w' - hi): hi + lo carries w' to
-//     2^-22 of itself. A code needs no conversion: masked in place it is the
-//     binary16 subnormal Q 2^(p - 24), exact in v_fma_mix_f32, and s_t takes
-//     the factor 2^(24 - p);
-//   * A: x' = x 2^(14 - Ex) in binary16: exact down to 2^-17 (bfloat16 has 8
-//     significant bits, binary16 11), to 2^-25 below.
-// Ex and Ew are running bounds per token and per row: the exponent of the
-// largest value of the quarter's first chunk plus 4 bits of headroom, moved
-// when a later chunk passes it or falls far below it; the accumulators, the
-// MFMAs' own, are then multiplied by the power of two (exact). On weights and
-// activations with outliers that happens in a few of the first chunks.
+//   * B: W~'s 24 significant bits as three bfloat16, 8 bits each, by cutting
+//     off: every product is exact and nothing of W~ is left out. A code needs
+//     no conversion: masked in place it is the binary16 subnormal
+//     Q 2^(p - 24), exact in v_fma_mix_f32, and s_t takes the factor
+//     2^(24 - p);
+//   * A: X as it is.
+// bfloat16 has binary32's range, so a value's neighbours along its row, or in
+// its tile, do not matter. Two binary16 operands and two passes took as long
+// (the activations then need converting, with running bounds on the ranges of
+// every token and row: 12288 x 4096, 2048 tokens, 4 stages 519 against 519
+// us; 5120 x 5120, 48 tokens 44.1 against 33.9) and held 22 bits of W~ at
+// best, fewer the wider the ranges.
 //
 // Accumulation order: the chunks of a row in 4 contiguous quarters
-// (ceil(chunks / 4) each), a quarter in stretches of 16 chunks, each
-// accumulated from 0 in chunk order (block by block, lo before hi), and the
-// stretches added in order. On rows of up to 8192 inputs a quarter is one
-// stretch and the order does not depend on the tile shape or on which waves
-// take the quarters: every token count gives the same results. On longer rows
-// quarters of their own waves are summed before they meet.
+// (ceil(chunks / 4) each), a quarter in stretches of 4 chunks, each
+// accumulated from 0 in chunk order (block by block, the least operand
+// first), and the stretches added in order. On rows of up to 2048 inputs a
+// quarter is one stretch and the order does not depend on the tile shape or
+// on which waves take the quarters: every token count gives the same results.
+// On longer rows quarters of their own waves are summed before they meet.
 //
-// What bounds it: vector issue. Per chunk of 16 rows a wave forms its B
-// operands with about 330 vector instructions at 4 stages (8 per element)
-// whatever the tokens, and its share of the activations' conversion with
-// about 100 per 16 tokens; a SIMD spends 4 to 5 cycles on each and 10 issue
-// cycles per MFMA, of 16 the MFMA takes. So the tile has as many tokens as
-// registers and LDS allow (256: 16 accumulators and 16 running sums) before
-// it has more rows, and calls with few tiles rather split the quarters over
-// waves than the tokens. Against the forms that multiply every stage's codes
-// (4 stages): 12288 x 4096, 2048 tokens, 786 -> 525 us (262 -> 393 TFLOP/s
-// of the product), 5120 x 5120, 48 tokens, 56.9 -> 43.8 us; against the
-// general kernel with groups of 64, 3 stages, 4096 x 4096, 1000 tokens, 508
-// -> 105 us.
+// What bounds it: vector issue and the matrix cores, with one or two of a
+// SIMD's waves to hide each behind the other. Per chunk of 16 rows a wave
+// forms its B operands with about 390 vector instructions at 4 stages (9 per
+// element and 3.5 to split it) whatever the tokens; a SIMD spends 4 to 5
+// cycles on each and 10 issue cycles per MFMA, of 16 the MFMA takes. So the
+// tile has as many tokens as registers and LDS allow (256: 16 accumulators
+// and 16 running sums) before it has more rows, and calls with few tiles
+// rather split the quarters over waves than the tokens.
 //
-// Tried and not kept: 32 x 32 x 16 MFMAs with two of a SIMD's waves in
-// alternate vector and matrix phases (562 us on the first of these, no room
-// for the quarters' running sums); the same phases with this tile, 64 inputs
-// per step (638 us: twice the barriers and per-step work); operand building
-// laid between the MFMAs of one wave by hand (822 us: one token tile in
-// flight).
+// Tried on the binary16 operands and not kept: 32 x 32 x 16 MFMAs with two of
+// a SIMD's waves in alternate vector and matrix phases (562 us on the first
+// shape above, no room for the quarters' running sums); the same phases with
+// this tile, 64 inputs per step (638 us: twice the barriers and per-step
+// work); operand building laid between the MFMAs of one wave by hand (822 us:
+// one token tile in flight). With the three bfloat16: a sum for every stretch
+// up to the end, so that rows of 8192 inputs too give the same results in
+// every shape (registers spilled: 5120 x 5120, 48 tokens 33.9 -> 36.7 us).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -59,23 +57,21 @@ namespace {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kZpSymmetric = 2;
 constexpr int kScaleF32 = 0, kScaleF16 = 1;
-constexpr uint32_t kHeadroom = 4;   // bits above a quarter's first maximum
-// Chunks accumulated before they are folded into the running sum: in one
-// stretch, a quarter of a long row loses more in its 16 x 50 accumulations
-// than the stage-sum forms do (25600 inputs, 1 stage, groups of 32: 6.3e-7
-// against 4.5e-7 off 64 bits).
-constexpr uint32_t kFoldChunks = 16;
+// Chunks accumulated before they are folded into the running sum. Error of
+// 12288 x 4096, 2048 tokens, 4 stages / 5120 x 25600, 192 tokens, 1 stage and
+// groups of 32, off 64 bits: 3.5e-7 / 4.5e-7 with 16 chunks, 3.5e-7 / 3.3e-7
+// with 8, 2.6e-7 / 2.6e-7 with 4, for 516 / 336, 514 / 337 and 519 / 341 us.
+constexpr uint32_t kFoldChunks = 4;
 
 __device__ __forceinline__ f32x4 mfma(const u32x4 &a, const u32x4 &b, const f32x4 &c)
 {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a),
-                                                  __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
 // fma(s, half of q, c) with the low / high binary16 of q (subnormals kept).
@@ -93,53 +89,29 @@ __device__ __forceinline__ float fma_hi(float s, uint32_t q, float c)
     return d;
 }
 
-// The binary16 pair of (a, b), rounded toward zero.
-__device__ __forceinline__ uint32_t pack_pair(float a, float b)
+// The bfloat16 pair of (a, b), cut off, and a and b less that (exact: what is
+// left has the 16, then 8, lower significant bits). neg_lo and neg_hi hold
+// the pairs (-1, 0) and (0, -1) in registers: written as a constant operand,
+// -1 would be taken as a binary32.
+__device__ __forceinline__ uint32_t cut_pair(float &a, float &b, uint32_t neg_lo, uint32_t neg_hi)
 {
-    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(a, b));
+    const uint32_t h = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+    const bf16x2 hv = __builtin_bit_cast(bf16x2, h);
+    a = __builtin_amdgcn_fdot2_f32_bf16(hv, __builtin_bit_cast(bf16x2, neg_lo), a, false);
+    b = __builtin_amdgcn_fdot2_f32_bf16(hv, __builtin_bit_cast(bf16x2, neg_hi), b, false);
+    return h;
 }
 
-// hi = the binary16 pair of (a, b), lo = that of what hi leaves (exact
-// differences). v_fma_mixlo / mixhi would write lo directly but issue at half
-// the rate of the three instructions used here.
-__device__ __forceinline__ void split_pair(float a, float b, uint32_t &hi, uint32_t &lo)
-{
-    hi = pack_pair(a, b);
-    float ra, rb;
-    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[0,0,1]" : "=v"(ra) : "v"(a), "v"(hi));
-    asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
-        : "=v"(rb) : "v"(b), "v"(hi));
-    lo = pack_pair(ra, rb);
-}
-
-__device__ __forceinline__ float pow2(int field)   // 2^(field - 127), 0 below
-{
-    return __uint_as_float((uint32_t)(field > 0 ? field : 0) << 23);
-}
-
-// A running bound (exponent field of a power of two that no value of the
-// chunk reaches twice) and the largest one of the quarter so far. A chunk
-// whose largest exponent field is e raises it when e passes it and lowers it
-// when e lies more than 12 bits below: kHeadroom bits above e within the
-// finite range, at least `least` (the scales then stay representable) and at
-// most 36 bits under the quarter's largest (two such factors leave the
-// accumulators, under 2^47 otherwise, finite). Values thus keep at least 2^-27
-// of their chunk's largest.
-struct Bound {
-    uint32_t at, peak;
-    __device__ __forceinline__ void update(uint32_t e, uint32_t least, bool fresh)
-    {
-        uint32_t b = e + kHeadroom;
-        b = b < 254u ? b : 254u;
-        b = b > e ? b : e;
-        b = b > least ? b : least;
-        const uint32_t low = b + 36u > peak ? b : peak - 36u;
-        if (fresh) at = peak = b;
-        else if (e > at) at = b;
-        else if (e + 12u < at && low < at) at = low;
-        peak = peak > at ? peak : at;
-    }
+// Scaling of a row's weights by a power of two where their magnitudes come
+// near the ends of binary32's range, so that neither the scales' factors in
+// dequant overflow nor the third operands underflow.
+struct Range {
+    float up, down;                      // applied to the scales, and to the sums
 };
+__device__ __forceinline__ Range range_of(int state)
+{
+    return state == 0 ? Range{1.0f, 1.0f} : state > 0 ? Range{0x1p-32f, 0x1p32f} : Range{0x1p64f, 0x1p-64f};
+}
 
 // A workgroup of WR x WQ waves owns 16 T tokens x 16 WR output rows: wave
 // (wr, wq) rows 16 wr .. 16 wr + 15 for all the tokens, over every quarter of
@@ -160,13 +132,7 @@ struct Tile {
     static constexpr int ZEROS = SCALES + PARAM_DMA * 256;
     static constexpr int W_BYTES = ZEROS + PARAM_DMA * 256;
     static constexpr int W_DMA = CODE_DMA + 2 * PARAM_DMA;
-    // per buffer and quarter: the activations of one chunk, then per token
-    // the bound's power of two and the factor to it from the last one, then
-    // per tile whether any factor is not 1
-    static constexpr int FX = TOK * 256;
-    static constexpr int RX = FX + TOK * 4;
-    static constexpr int FLAG = RX + TOK * 4;
-    static constexpr int XB = FLAG + ((T * 4 + 15) / 16) * 16;
+    static constexpr int XB = TOK * 256;                     // per buffer and quarter
     static constexpr int W_BASE = 2 * WQ * XB;
     static constexpr int BYTES = W_BASE + WR * WQ * W_BYTES;
     static_assert(BYTES <= 160 * 1024, "LDS of a compute unit");
@@ -191,6 +157,9 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
     const int n = lane & 15;            // A row (token of a tile), B column (row)
     const int j = lane >> 4;            // k-slice
     const bool sym = zero_point == kZpSymmetric;
+    uint32_t neg_lo, neg_hi;
+    asm volatile("s_mov_b32 %0, 0xbf80" : "=s"(neg_lo));
+    asm volatile("s_mov_b32 %0, 0xbf800000" : "=s"(neg_hi));
 
     const int64_t m0 = (int64_t)(blockIdx.x / row_tiles) * L::TOK;
     const int64_t o0 = (int64_t)(blockIdx.x % row_tiles) * (16 * WR) + 16 * wr;
@@ -279,78 +248,6 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
         }
     };
 
-    // Rewrites this wave's token tiles of buffer b in place as binary16 with
-    // the tokens' bounds so far and publishes the bounds; values outside a
-    // token's range (or a quarter's first chunk) change the bounds first.
-    Bound ex[L::PT];
-#pragma unroll
-    for (int q = 0; q < L::PT; ++q) ex[q] = {14u, 14u};
-    auto prepare = [&](int b, bool fresh) {
-        char *lb = xbuf(b);
-#pragma unroll
-        for (int q = 0; q < L::PT; ++q) {
-            const int tt = t0 + q;
-            char *xt = lb + (16 * tt + n) * 256;
-            u32x4 v[4], h[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                v[i] = *reinterpret_cast<const u32x4 *>(xt + 16 * ((4 * j + i) ^ n));
-            uint32_t m[4] = {0, 0, 0, 0};
-            const float sc = pow2(268 - (int)ex[q].at);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    h[i][p] = pack_pair(__uint_as_float(v[i][p] << 16) * sc,
-                                        __uint_as_float(v[i][p] & 0xFFFF0000u) * sc);
-                    // the pairs' largest magnitudes (a NaN stays one)
-                    asm("v_pk_maximum3_f16 %0, %0, %1, %1 neg_lo:[0,0,1] neg_hi:[0,0,1]"
-                        : "+v"(m[p]) : "v"(h[i][p]));
-                }
-#pragma unroll
-            for (int p = 1; p < 4; ++p)
-                asm("v_pk_maximum3_f16 %0, %0, %1, %1 neg_lo:[0,0,1] neg_hi:[0,0,1]"
-                    : "+v"(m[0]) : "v"(m[p]));
-            const uint32_t ml = m[0] & 0x7FFFu, mh = (m[0] >> 16) & 0x7FFFu;
-            const uint32_t old = ex[q].at, top = ml > mh ? ml : mh;
-            // 2^15, or 2^3 with the lane's 32 inputs not all zeros
-            const bool outside = top >= 0x7800u || (top < 0x4800u && top != 0u);
-            uint32_t any = 0;
-            if (fresh || __ballot(outside) != 0) {
-                u16x2 mv = {0, 0};
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int p = 0; p < 4; ++p)
-                        mv = __builtin_elementwise_max(
-                            mv, __builtin_bit_cast(u16x2, v[i][p] & 0x7FFF7FFFu));
-                uint32_t mx = mv.x > mv.y ? mv.x : mv.y;
-                uint32_t o = (uint32_t)__shfl_xor((int)mx, 16);
-                mx = mx > o ? mx : o;
-                o = (uint32_t)__shfl_xor((int)mx, 32);
-                mx = mx > o ? mx : o;
-                if (mx != 0u || fresh) ex[q].update(mx >> 7, 14u, fresh);
-                any = !fresh && __ballot(ex[q].at != old) != 0;
-                const float s1 = pow2(268 - (int)ex[q].at);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int p = 0; p < 4; ++p)
-                        h[i][p] = pack_pair(__uint_as_float(v[i][p] << 16) * s1,
-                                            __uint_as_float(v[i][p] & 0xFFFF0000u) * s1);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                *reinterpret_cast<u32x4 *>(xt + 16 * ((4 * j + i) ^ n)) = h[i];
-            if (lane < 16) {
-                *reinterpret_cast<float *>(lb + L::FX + 4 * (16 * tt + n)) = __uint_as_float(ex[q].at << 23);
-                *reinterpret_cast<float *>(lb + L::RX + 4 * (16 * tt + n)) =
-                    any ? pow2(127 + (int)old - (int)ex[q].at) : 1.0f;
-                *reinterpret_cast<uint32_t *>(lb + L::FLAG + 4 * tt) = any;
-            }
-        }
-    };
-
     f32x4 acc[T], run[T];
 #pragma unroll
     for (int q = 0; q < T; ++q) {
@@ -372,12 +269,35 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
             zw[t] = *reinterpret_cast<const uint32_t *>(my_w + L::ZEROS + e);
         }
     };
-    // Scaled stage scales and zero terms of the lane's row for the chunk; if
-    // a row's bound changed, the accumulators are rescaled.
-    Bound ew = {32u, 32u};
+    // Adds the accumulators of the lanes with yes to their running sums.
+    int state = 0;                      // of the lane's row: Range
+    auto fold = [&](bool yes) {
+        const float down = range_of(state).down;
+#pragma unroll
+        for (int q = 0; q < T; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                run[q][i] = yes ? run[q][i] + acc[q][i] * down : run[q][i];
+                acc[q][i] = yes ? 0.0f : acc[q][i];
+            }
+    };
+    auto fold_all = [&]() {
+        if (__ballot(state != 0) != 0) {
+            fold(true);
+            return;
+        }
+#pragma unroll
+        for (int q = 0; q < T; ++q) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) run[q][i] = run[q][i] + acc[q][i];
+            acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    // Stage scales and zero terms of the lane's row for the chunk; if the
+    // row's range changed, its accumulators are folded first.
     float sv[K][3], cz = 0.0f;
-    auto params = [&](bool fresh) {
-        float s[K], z[K], M = 0.0f;
+    auto params = [&]() {
+        float s[K], z[K], m = 0.0f;
 #pragma unroll
         for (int t = 0; t < K; ++t) {
             s[t] = scale_type == kScaleF32 ? __uint_as_float(sw[t])
@@ -385,31 +305,29 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
                        ? (float)__builtin_bit_cast(_Float16, (uint16_t)(sw[t] & 0xFFFFu))
                        : __uint_as_float(sw[t] << 16);
             z[t] = sym ? 2.0f : __uint_as_float(zw[t]);
-            M = __builtin_fmaf(fabsf(s[t]), 3.0f + fabsf(z[t]), M);
+            m = __builtin_fmaf(fabsf(s[t]), 3.0f + fabsf(z[t]), m);
         }
-        uint32_t e = (__float_as_uint(M) >> 23) & 0xFFu;
-        if constexpr (GPC >= 2) {
-            const uint32_t o = (uint32_t)__shfl_xor((int)e, 32);
-            e = e > o ? e : o;
+        // (bit patterns of non-negative floats compare like the floats)
+        uint32_t e = __float_as_uint(m);
+        const bool far = e != 0u && (e >= (223u << 23) || e < (63u << 23));
+        if (__ballot(far || state != 0) != 0) {
+            if constexpr (GPC >= 2) {
+                const uint32_t o = (uint32_t)__shfl_xor((int)e, 32);
+                e = e > o ? e : o;
+            }
+            if constexpr (GPC >= 4) {
+                const uint32_t o = (uint32_t)__shfl_xor((int)e, 16);
+                e = e > o ? e : o;
+            }
+            const int now = e == 0u ? state : e >= (223u << 23) ? 1 : e < (63u << 23) ? -1 : 0;
+            fold(now != state);
+            state = now;
         }
-        if constexpr (GPC >= 4) {
-            const uint32_t o = (uint32_t)__shfl_xor((int)e, 16);
-            e = e > o ? e : o;
-        }
-        const uint32_t old = ew.at;
-        if (e != 0u || fresh) ew.update(e, 32u, fresh);
-        if (__ballot(!fresh && ew.at != old) != 0) {
-            const float f = pow2(127 + (int)old - (int)ew.at);
-#pragma unroll
-            for (int q = 0; q < T; ++q)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[q][i] *= f;
-        }
-        const float fs = pow2(268 - (int)ew.at);
+        const float up = range_of(state).up;
         float c = 0.0f;
 #pragma unroll
         for (int t = 0; t < K; ++t) {
-            const float ss = s[t] * fs;
+            const float ss = s[t] * up;
             c = __builtin_fmaf(-ss, z[t], c);
             sv[t][0] = ss * 0x1p20f;
             sv[t][1] = ss * 0x1p18f;
@@ -419,7 +337,7 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
     };
 
     // B operands of blocks 2 h, 2 h + 1 from the lane's code word h.
-    u32x4 bh[2], bl[2];
+    u32x4 bw[3][2];
     auto dequant = [&](int h) {
         float w[16];
 #pragma unroll
@@ -440,12 +358,10 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                uint32_t hi, lo;
-                split_pair(w[8 * b + 2 * v], w[8 * b + 2 * v + 1], hi, lo);
-                bh[b][v] = hi;
-                bl[b][v] = lo;
-            }
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    bw[p][b][v] = cut_pair(w[8 * b + 2 * v], w[8 * b + 2 * v + 1], neg_lo, neg_hi);
     };
 
     uint32_t q_left = per_q;            // chunks left in the quarter
@@ -454,40 +370,20 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
         if (stages_x) {
             issue_x(c_begin, 0);
             wait_vm<0>();
-            prepare(0, true);
         }
     }
     for (uint32_t it = 0; it < steps; ++it) {
         const uint32_t c = c_begin + it;
         const int b = (int)(it & 1);
-        // every wave has prepared its tiles of this chunk, and is done with
-        // the other buffer
+        // every wave's activations of this chunk have landed, and every wave
+        // is done with the other buffer
         __syncthreads();
         if (c >= c_end) continue;
-        const bool first = q_left == per_q;
         const bool last = q_left == 1 || c + 1 == c_end;   // of the quarter
         wait_vm<0>();                   // the package words have landed
         read_w();
         const char *lb = xbuf(b);
-        u32x4 flags[(T + 3) / 4];
-#pragma unroll
-        for (int q = 0; q < (T + 3) / 4; ++q)
-            flags[q] = *reinterpret_cast<const u32x4 *>(lb + L::FLAG + 16 * q);
-        if (!first) {
-            uint32_t changed = 0;
-#pragma unroll
-            for (int q = 0; q < T; ++q) changed |= flags[q / 4][q % 4];
-            if (__builtin_amdgcn_readfirstlane(changed)) {
-                // tokens whose bound changed
-#pragma unroll
-                for (int q = 0; q < T; ++q) {
-                    const f32x4 f = *reinterpret_cast<const f32x4 *>(lb + L::RX + 4 * (16 * q + 4 * j));
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[q][i] *= f[i];
-                }
-            }
-        }
-        params(first);
+        params();
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             dequant(h);
@@ -506,29 +402,17 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const u32x4 a = *reinterpret_cast<const u32x4 *>(xt + 16 * ((4 * j + 2 * h + i) ^ n));
-                    acc[q] = mfma(a, bl[i], acc[q]);
-                    acc[q] = mfma(a, bh[i], acc[q]);
+                    acc[q] = mfma(a, bw[2][i], acc[q]);
+                    acc[q] = mfma(a, bw[1][i], acc[q]);
+                    acc[q] = mfma(a, bw[0][i], acc[q]);
                 }
             }
         }
         --q_left;
-        if (last || (per_q - q_left) % kFoldChunks == 0) {
-            // end of the quarter or of a stretch of it: fold it into the
-            // running sum (the bounds run on within the quarter)
-            const float fw = pow2((int)ew.at - 28);
-#pragma unroll
-            for (int q = 0; q < T; ++q) {
-                const f32x4 fx = *reinterpret_cast<const f32x4 *>(lb + L::FX + 4 * (16 * q + 4 * j));
-#pragma unroll
-                for (int i = 0; i < 4; ++i) run[q][i] = run[q][i] + (acc[q][i] * fw) * fx[i];
-                acc[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
-            }
-            if (last) q_left = per_q;
-        }
-        if (stages_x) {
-            wait_vm<L::W_DMA>();        // the next chunk's activations have landed
-            prepare(b ^ 1, last);
-        }
+        // end of the quarter or of a stretch of it
+        if (last || (per_q - q_left) % kFoldChunks == 0) fold_all();
+        if (last) q_left = per_q;
+        if (stages_x) wait_vm<L::W_DMA>();   // the next chunk's activations have landed
     }
     // no load may still write this workgroup's LDS once it ends or reuses it
     wait_vm<0>();
@@ -610,27 +494,32 @@ hipError_t launch_k(const Call &c)
 
 // Tile shapes: A, B, C stage all quarters in turn (8 row waves, 256 / 128 /
 // 64 tokens), D, E, F give each quarter its own waves (32 rows x 64 tokens,
-// 32 x 32, 64 x 32), for calls with too few tiles to fill the chip. One
-// workgroup runs per compute unit, so a call costs its rounds of workgroups
-// times the shape's time per round. kCost is that time in hundredths of B's:
-// measured at 4096 inputs, 4 stages (groups of 128): 158, 103, 75, 34, 25.5,
-// 37 us (158, 100, 69, 33, 24, 35 us at 3 stages and groups of 64).
+// 32 x 32, 64 x 32), for calls with too few tiles to fill the chip. A compute
+// unit runs one workgroup, or two of C and, at 1 and 2 stages, of E (LDS), so
+// a call costs its rounds of workgroups times the shape's time per round, with
+// one (kCost) or two (kPair) to a compute unit: in tenths of a microsecond per
+// 4096 inputs by stages, measured with groups of 64 and 128 on 4096 to 16384
+// rows at 64 to 2048 tokens, packages read from HBM.
 enum Shape { A, B, C, D, E, F, kShapes };
 constexpr int kRows[kShapes] = {128, 128, 128, 32, 32, 64};
 constexpr int kTokens[kShapes] = {256, 128, 64, 64, 32, 32};
-constexpr int kCost[kShapes] = {154, 100, 71, 33, 24, 36};
+constexpr int kCost[4][kShapes] = {{1560, 900, 570, 205, 160, 240}, {1630, 970, 650, 230, 190, 280},
+                                   {1720, 1060, 760, 260, 225, 340}, {1830, 1160, 870, 290, 255, 450}};
+constexpr int kPair[4][kShapes] = {{0, 0, 1030, 0, 250, 0}, {0, 0, 1210, 0, 300, 0},
+                                   {0, 0, 1360, 0, 0, 0}, {0, 0, 1540, 0, 0, 0}};
 
-// The cheapest shape and its cost (per 4096 inputs). A and D's buffers do not
-// fit the LDS with groups of 32.
-Shape cheapest(int64_t rows, int64_t n_tokens, int G, int cus, int64_t *cost)
+// The cheapest shape and its cost (tenths of a microsecond per 4096 inputs).
+Shape cheapest(int64_t rows, int64_t n_tokens, int k, int cus, int64_t *cost)
 {
     Shape best = B;
     *cost = INT64_MAX;
     for (int s = kShapes - 1; s >= 0; --s) {
-        if (G == 32 && (s == A || s == D)) continue;
         const int64_t tiles = ((rows + kRows[s] - 1) / kRows[s]) *
                               ((n_tokens + kTokens[s] - 1) / kTokens[s]);
-        const int64_t c = (tiles + cus - 1) / cus * kCost[s];
+        const int64_t one = kCost[k - 1][s], pair = kPair[k - 1][s];
+        const int64_t left = tiles % (2 * cus);
+        const int64_t c = pair == 0 ? (tiles + cus - 1) / cus * one
+                                    : tiles / (2 * cus) * pair + (left == 0 ? 0 : left <= cus ? one : pair);
         if (c < *cost) {
             *cost = c;
             best = (Shape)s;
@@ -643,26 +532,23 @@ template <int GPC>
 hipError_t launch_g(const Call &c, Shape s)
 {
     switch (s) {
+    case A: return launch_k<GPC, 8, 1, 16>(c);
     case B: return launch_k<GPC, 8, 1, 8>(c);
     case C: return launch_k<GPC, 8, 1, 4>(c);
+    case D: return launch_k<GPC, 2, 4, 4>(c);
     case E: return launch_k<GPC, 2, 4, 2>(c);
     case F: return launch_k<GPC, 4, 4, 2>(c);
-    default: break;
+    default: return hipErrorInvalidValue;
     }
-    if constexpr (GPC < 4) {
-        if (s == A) return launch_k<GPC, 8, 1, 16>(c);
-        if (s == D) return launch_k<GPC, 2, 4, 4>(c);
-    }
-    return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-int64_t split_cost(int64_t rows, int64_t n_tokens, int cus)
+int64_t split_cost(int64_t rows, int64_t n_tokens, int k, int cus)
 {
     int64_t cost;
-    cheapest(rows, n_tokens, 128, cus, &cost);
-    return 10 * cost;
+    cheapest(rows, n_tokens, k, cus, &cost);
+    return cost;
 }
 
 bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus)
@@ -674,32 +560,24 @@ bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_token
     if (G == 128) {
         if (n_tokens < kPrefillMinTokens && linear_prefill_fits(rows, cols, G, k, n_tokens, cus))
             return false;
-        // Below 3 stages the stage products take no more passes than the
-        // split's two and need no operand arithmetic: never ahead there.
+        // One and two stages stay with the forms that multiply the stages'
+        // codes: no more passes than three, and no operand arithmetic. (Ahead
+        // from 128 x 128 tiles on: 12288 x 4096, 128 tokens, 2 stages 55
+        // against 63 us. With few tiles this form would be: 4096 x 4096, 64 /
+        // 128 tokens, 2 stages 19 / 23 against 23 / 37.)
         if (k < 3) return false;
         // Against the prefill form: ahead once the 128 x 128 tiles (B) give
         // nearly every compute unit one. 4 / 3 stages: 4096 x 4096, 1024
-        // tokens 114 / 107 against 142 / 110 us, 12288 x 4096, 500 tokens 171
-        // / 160 against 257 / 201, 2048 tokens 529 / 502 against 827 / 656;
-        // with half as many tiles (4096 x 4096, 500 tokens) 86 / 74 against
+        // tokens 114 / 107 against 142 / 110 us, 12288 x 4096, 500 tokens 163
+        // / 153 against 257 / 201, 2048 tokens 519 / 496 against 769 / 656;
+        // with half as many tiles (4096 x 4096, 500 tokens) 88 / 79 against
         // 86 / 71.
         if (n_tokens >= kPrefillMinTokens) {
             const int64_t tiles = ((rows + 127) / 128) * ((n_tokens + 127) / 128);
             return 8 * tiles >= (k == 4 ? 7 : 8) * (int64_t)cus;
         }
     }
-    // Against the general kernel, which takes 16 tokens per pass over the
-    // package with 16 rows per workgroup: its passes cost a fixed part and one
-    // per round of workgroups, here in tenths of the unit of kCost, measured
-    // on 4096 and 12288 rows of 4096 inputs at 17 to 128 tokens.
-    static constexpr int kPerRound[3][4] = {{36, 90, 145, 190}, {18, 40, 61, 80}, {0, 0, 65, 60}};
-    const int64_t passes = (n_tokens + 15) / 16;
-    const int64_t rounds = ((rows + 15) / 16 + cus - 1) / cus;
-    const int per_round = kPerRound[G == 32 ? 0 : G == 64 ? 1 : 2][k - 1];
-    const int64_t general = passes * ((k == 1 ? 45 : 15) + rounds * per_round);
-    int64_t cost;
-    cheapest(rows, n_tokens, G, cus, &cost);
-    return 10 * cost < general;
+    return split_cost(rows, n_tokens, k, cus) < general_cost(rows, n_tokens, G, k, cus);
 }
 
 hipError_t launch_linear_split(const uint32_t *codes, const void *scales, const float *zeros,
@@ -710,7 +588,7 @@ hipError_t launch_linear_split(const uint32_t *codes, const void *scales, const 
     const Call c = {codes, static_cast<const char *>(scales), zeros, rows, cols, k, zero_point,
                     scale_type, X, n_tokens, Y, stream};
     int64_t cost;
-    const Shape shape = cheapest(rows, n_tokens, G, cus, &cost);
+    const Shape shape = cheapest(rows, n_tokens, k, cus, &cost);
     switch (G) {
     case 32: return launch_g<4>(c, shape);
     case 64: return launch_g<2>(c, shape);

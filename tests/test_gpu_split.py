@@ -4,14 +4,18 @@ oracle's Eq. 20 product in float64.
 
 * exact: power-of-two scales, integer or dyadic zero-points and
   small-integer activations make every intermediate exactly representable
-  (the weight is a multiple of 2^-4 below 4, so its first binary16 operand
-  holds it), so the sampled outputs must equal the exact value bit for bit:
+  (the weight is a multiple of 2^-4 below 4, so its first two bfloat16
+  operands hold it), so the sampled outputs must equal the exact value bit for bit:
   every tile shape, ragged rows, tokens and last chunks, quarters of unequal
   length and empty ones, every stage count and format;
 * bounded: realistic packages, and scales and activations whose ranges move
-  by many binades along a row (the running bounds rise and fall), stay within
-  the bound of include/rrq.h;
-* the results do not depend on the tile shape a call takes;
+  by many binades along a row, all tokens alike or each its own way, and
+  between the groups of one chunk, with the scales' range against the
+  activations' or near the ends of binary32's, stay within the bound of
+  include/rrq.h, as do rows longer than 8192 inputs in every way of splitting
+  a row over waves;
+* the results do not depend on the tile shape a call takes (rows of up to
+  2048 inputs), nor a token's on the other tokens;
 * a token holding an infinity or a NaN does not touch the others.
 Packages come from the oracle or a seeded generator, never from the GPU.
 """
@@ -191,3 +195,110 @@ def test_split_extreme_token(gpu, value):
         ref = npo.linear(codes, s, z, rows, cols, G, k, bits.reshape(-1))
         tol = _bound(s, z, rows, cols, G, k, bits.reshape(-1), np.arange(rows))
         assert np.all(np.abs(y[7].astype(np.float64) - ref[7]) <= tol[7])
+
+
+# Which waves take a row's chunks: each quarter its own (40 and 72 tokens, 300
+# rows) or all in turn (1000 tokens, 4090 rows).
+_SPLITS = [(300, 40), (300, 72), (4090, 1000)]
+
+
+def _ranged(rows, cols, G, M, fx, fs, seed):
+    """A package and activations with chunk or group factors fx (of the
+    inputs) and fs (of the groups), both powers of two along the row."""
+    rng = np.random.default_rng(seed)
+    w = (rng.standard_normal(rows * cols) * 0.02).astype(np.float32)
+    codes, s, z = oracle.c_construct(npo.f32_to_bf16_bits(w), G, 4)
+    x = rng.standard_normal((M, cols)).astype(np.float32)
+    with np.errstate(over="raise"):
+        x = (x.astype(np.float64) * fx[None]).astype(np.float32)
+        s = (s.reshape(4, rows, cols // G).astype(np.float64) * fs[None, None]).astype(np.float32)
+    return codes, s.reshape(4, -1), z, npo.f32_to_bf16_bits(x)
+
+
+def _check_bound(gpu, codes, s, z, rows, cols, G, k, xb, what):
+    idx = _sample(rows, 1)
+    y = _run(gpu, codes, s, z, rows, cols, G, k, xb)
+    ref = npo.linear(codes, s, z, rows, cols, G, k, xb, row_index=idx)
+    tol = _bound(s, z, rows, cols, G, k, xb, idx)
+    worst = np.max(np.abs(y[:, idx].astype(np.float64) - ref) / tol)
+    _log(f"split {what}: max err / bound = {worst:.3g}")
+    assert worst <= 1, f"{what}: {worst}"
+    return y
+
+
+@pytest.mark.parametrize("rows,M", _SPLITS)
+@pytest.mark.parametrize("G", [32, 64, 128])
+@pytest.mark.parametrize("R", [24, 34, 36, 60])
+def test_split_ranges_drop_along_a_row(gpu, rows, M, G, R):
+    """The first chunk of every quarter is 2^R larger in the activations and
+    2^R smaller in the scales (all tokens and rows alike)."""
+    cols, k = 2048, 4
+    chunk = np.where(np.arange(16) % 4 == 0, 2.0 ** R, 1.0)
+    pkg = _ranged(rows, cols, G, M, np.repeat(chunk, 128), np.repeat(1 / chunk, 128 // G), R)
+    _check_bound(gpu, *pkg[:3], rows, cols, G, k, pkg[3], f"drop 2^{R} G={G} M={M}")
+
+
+@pytest.mark.parametrize("rows,M", _SPLITS)
+def test_split_ranges_drop_after_zero_weights(gpu, rows, M):
+    """A first chunk of large activations whose weights are all zero."""
+    cols, G, k = 1024, 128, 4
+    fx = np.repeat(np.where(np.arange(8) % 2 == 0, 2.0 ** 40, 1.0), 128)
+    fs = np.where(np.arange(8) % 2 == 0, 0.0, 1.0)
+    pkg = _ranged(rows, cols, G, M, fx, fs, 5)
+    _check_bound(gpu, *pkg[:3], rows, cols, G, k, pkg[3], f"zero weights M={M}")
+
+
+@pytest.mark.parametrize("rows,M", _SPLITS)
+@pytest.mark.parametrize("G", [32, 64])
+@pytest.mark.parametrize("R", [12, 22, 30, 40, 80])
+def test_split_ranges_between_groups_of_a_chunk(gpu, rows, M, G, R):
+    """Neighbouring groups 2^R apart, the activations one way and the scales
+    the other; and the large activations over groups of scale 0."""
+    cols, k = 640, 2
+    far = np.arange(cols // G) % 2 == 0
+    fx = np.repeat(np.where(far, 2.0 ** R, 1.0), G)
+    pkg = _ranged(rows, cols, G, M, fx, np.where(far, 2.0 ** -R, 1.0), R + G)
+    _check_bound(gpu, *pkg[:3], rows, cols, G, k, pkg[3], f"in-chunk 2^{R} G={G} M={M}")
+    pkg = _ranged(rows, cols, G, M, fx, np.where(far, 0.0, 1.0), R + G)
+    _check_bound(gpu, *pkg[:3], rows, cols, G, k, pkg[3], f"in-chunk 2^{R}, zero scales G={G} M={M}")
+
+
+@pytest.mark.parametrize("rows,M", _SPLITS)
+@pytest.mark.parametrize("G", [32, 128])
+@pytest.mark.parametrize("scale", [2.0 ** 104, 2.0 ** 90, 2.0 ** -60, 2.0 ** -72, 2.0 ** -115, "moving"])
+def test_split_ranges_near_the_ends(gpu, rows, M, G, scale):
+    """Scales near binary32's ends with activations that bring the products
+    back, and a row that goes through all of them."""
+    cols, k = 1024, 4
+    f = (np.array([1, 2.0 ** 104, 2.0 ** -115, 2.0 ** -70, 0, 2.0 ** 90, 2.0 ** -60, 2.0 ** -1])
+         if scale == "moving" else np.full(8, scale))
+    inv = np.where(f == 0, 1, 1 / np.where(f == 0, 1, f))
+    pkg = _ranged(rows, cols, G, M, np.repeat(inv, 128), np.repeat(f, 128 // G), G)
+    y = _check_bound(gpu, *pkg[:3], rows, cols, G, k, pkg[3], f"scale {scale} G={G} M={M}")
+    assert np.all(np.isfinite(y))
+
+
+@pytest.mark.parametrize("rows,M", _SPLITS)
+@pytest.mark.parametrize("G,cols,k", [(128, 9216, 4), (128, 20608, 3), (64, 8896, 2), (32, 10272, 1)])
+def test_split_long_rows_within_bound(gpu, rows, M, G, cols, k):
+    pkg = _ranged(rows, cols, G, M, np.ones(cols), np.ones(cols // G), cols)
+    _check_bound(gpu, *pkg[:3], rows, cols, G, k, pkg[3], f"cols={cols} G={G} M={M}")
+
+
+@pytest.mark.parametrize("G,R", [(128, 35), (64, 35), (32, 20)])
+def test_split_token_does_not_depend_on_the_others(gpu, G, R):
+    """A token whose ranges drop along the row keeps its bits whether the
+    other tokens of its tile do as it does, or not, and wherever it stands."""
+    rows, cols, M, k = 300, 2048, 72, 4
+    chunk = np.where(np.arange(16) % 4 == 0, 2.0 ** R, 1.0)
+    codes, s, z, xb = _ranged(rows, cols, G, M, np.repeat(chunk, 128), np.repeat(1 / chunk, 128 // G), 3)
+    y = _run(gpu, codes, s, z, rows, cols, G, k, xb)
+    rng = np.random.default_rng(4)
+    other = npo.f32_to_bf16_bits((rng.standard_normal((M, cols)) *
+                                  2.0 ** rng.integers(-40, 41, (M, cols // 128)).repeat(128, axis=1)
+                                  ).astype(np.float32)).reshape(M, cols)
+    for at in (0, 17, 71):
+        mixed = other.copy()
+        mixed[at] = xb.reshape(M, cols)[17]
+        ym = _run(gpu, codes, s, z, rows, cols, G, k, mixed.reshape(-1))
+        assert np.array_equal(ym[at].view(np.uint32), y[17].view(np.uint32)), at
