@@ -80,13 +80,15 @@ hipError_t launch_linear_batch(const uint32_t *codes, const void *scales, const 
                                const uint16_t *X, int64_t n_tokens, float *Y, int cus,
                                hipStream_t stream);
 // The prefill form (groups of 128, at least kPrefillMinTokens tokens, or
-// more than 16 where the rows give enough tiles:
-// linear_prefill_fits;
-// 128-token x 128-row tiles when they still give every compute unit one,
-// else 64 x 64). Measured against the general kernel on the Qwen3-8B shapes:
-// from 128 tokens it is faster on all of them (2-3x from 256); below that a
-// matrix of a few thousand rows gives too few tiles to fill the GPU.
+// more than 16 where the rows give enough tiles: linear_prefill_fits).
+// Measured against the general kernel on the Qwen3-8B shapes: from 128 tokens
+// it is faster on all of them (2-3x from 256); below that a matrix of a few
+// thousand rows gives too few tiles to fill the GPU.
 constexpr int kPrefillMinTokens = 128;
+// The tile a call of this form runs and, below kPrefillMinTokens, its time
+// (in the unit of split_cost; else 0).
+enum class PrefillTile { Small, Large, Wide };
+PrefillTile prefill_tile(int64_t rows, int64_t n_tokens, int k, int cus, int64_t *cost);
 bool linear_prefill_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus);
 hipError_t launch_linear_prefill(const uint32_t *codes, const void *scales, const float *zeros,
                                  int64_t rows, int64_t cols, int k, int zero_point,

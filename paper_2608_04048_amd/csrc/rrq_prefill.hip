@@ -423,42 +423,75 @@ hipError_t launch_k(const uint32_t *codes, const char *scales, const float *zero
     }
 }
 
-// Tile shape: the large tile (8 waves, 128 rows x 128 tokens: every code
-// operand serves 8 token tiles) when it gives at least 3/4 of the compute
-// units a workgroup, else the small one (4 waves, 64 rows x 64 tokens).
-// Measured on 4096 x 4096, 12288 x 4096 and 4096 x 12288 from 256 to 2048
-// tokens, the large tile is the faster one exactly there. Up to 64 tokens it
-// would be half padding.
-bool large_tiles(int64_t rows, int64_t n_tokens, int cus)
-{
-    return n_tokens > 64 && 4 * ((rows + 127) / 128) * ((n_tokens + 127) / 128) >= 3 * (int64_t)cus;
-}
-
-// One stage: waves of 32 rows (8 waves, 256 rows x 128 tokens), so that each
-// A operand read from LDS serves two row tiles, when that still gives every
-// compute unit a workgroup (30% faster than 16-row waves on the three
-// shapes at 2048 tokens; slower where it leaves compute units idle). With
-// more stages the 32-row waves' code operands do not fit the registers of
-// 128 tokens, and 64 tokens were slower than 16-row waves.
-bool wide_tiles(int k, int64_t rows, int64_t n_tokens, int cus)
-{
-    return k == 1 && ((rows + 255) / 256) * ((n_tokens + 127) / 128) >= cus;
-}
-
 template <bool DEF>
 hipError_t launch_d(const uint32_t *codes, const char *scales, const float *zeros, int64_t rows,
                     int64_t cols, int k, int zp, int sdt, const uint16_t *X, int64_t n_tokens,
                     float *Y, int cus, hipStream_t stream)
 {
-    if (wide_tiles(k, rows, n_tokens, cus))
+    int64_t cost;
+    switch (prefill_tile(rows, n_tokens, k, cus, &cost)) {
+    case PrefillTile::Wide:
         return launch_t<1, DEF, 8, 8, 2>(codes, scales, zeros, rows, cols, zp, sdt, X, n_tokens, Y,
                                          stream);
-    return large_tiles(rows, n_tokens, cus)
-        ? launch_k<DEF, 8, 8>(codes, scales, zeros, rows, cols, k, zp, sdt, X, n_tokens, Y, stream)
-        : launch_k<DEF, 4, 4>(codes, scales, zeros, rows, cols, k, zp, sdt, X, n_tokens, Y, stream);
+    case PrefillTile::Large:
+        return launch_k<DEF, 8, 8>(codes, scales, zeros, rows, cols, k, zp, sdt, X, n_tokens, Y,
+                                   stream);
+    default:
+        return launch_k<DEF, 4, 4>(codes, scales, zeros, rows, cols, k, zp, sdt, X, n_tokens, Y,
+                                   stream);
+    }
 }
 
 }  // namespace
+
+// Tile shape: the large tile (8 waves, 128 rows x 128 tokens: every code
+// operand serves 8 token tiles), the small one (4 waves, 64 rows x 64 tokens)
+// or, at one stage, the wide one (8 waves of 32 rows, 256 rows x 128 tokens,
+// so that each A operand read from LDS serves two row tiles; with more stages
+// the 32-row waves' code operands do not fit the registers of 128 tokens, and
+// 64 tokens were slower than 16-row waves).
+PrefillTile prefill_tile(int64_t rows, int64_t n_tokens, int k, int cus, int64_t *cost)
+{
+    const int64_t small_rows = (rows + 63) / 64, large_rows = (rows + 127) / 128,
+                  wide_rows = (rows + 255) / 256;
+    *cost = 0;
+    if (n_tokens >= kPrefillMinTokens) {
+        // From 128 tokens: wide where it gives every compute unit a
+        // workgroup (30% faster than 16-row waves on three shapes at 2048
+        // tokens; slower where it leaves compute units idle), large where it
+        // gives at least 3/4 of them one (measured on 4096 x 4096, 12288 x
+        // 4096 and 4096 x 12288 from 256 to 2048 tokens, the faster one
+        // exactly there).
+        const int64_t token_tiles = (n_tokens + 127) / 128;
+        if (k == 1 && wide_rows * token_tiles >= cus) return PrefillTile::Wide;
+        return 4 * large_rows * token_tiles >= 3 * (int64_t)cus ? PrefillTile::Large
+                                                                : PrefillTile::Small;
+    }
+    // Fewer tokens: the cheapest by the rounds of workgroups and the time of
+    // one, in tenths of a microsecond per 4096 inputs by stages. Small tiles:
+    // one per compute unit, two that share their codes (two token tiles), or
+    // two row tiles. Measured small / large / wide on rows of 2048 inputs: 2
+    // stages, 80 tokens, 16384 rows 29 / 40 us, 16448 rows 44 / 40, 30000 rows
+    // 56 / 43, 33000 rows 70 / 82; 4 stages, 80 tokens, 20000 rows 65 / 65,
+    // 33000 rows 106 / 132; on rows of 1024 inputs, one stage, 65536 rows, 48
+    // tokens 26.0 / 37.5 / 26.5, 100 tokens 49 / 40 / 30; 70000 rows, 48 tokens
+    // 33 / 54 / 48.
+    static constexpr int kSmall[3][4] = {{318, 378, 446, 505}, {480, 560, 646, 782},
+                                         {440, 540, 680, 830}};
+    static constexpr int kLarge[4] = {620, 760, 1025, 1426}, kWide = 900;
+    const int64_t tiles = small_rows * ((n_tokens + 63) / 64), left = tiles % (2 * cus);
+    const int64_t pair = kSmall[small_rows <= cus ? 1 : 2][k - 1];
+    const int64_t small = tiles / (2 * cus) * pair +
+                          (left == 0 ? 0 : left <= cus ? kSmall[0][k - 1] : pair);
+    const int64_t large = (large_rows + cus - 1) / cus * kLarge[k - 1];
+    const int64_t wide = k == 1 ? (wide_rows + cus - 1) / cus * kWide : INT64_MAX;
+    *cost = small < large ? small : large;
+    if (wide <= *cost) {
+        *cost = wide;
+        return PrefillTile::Wide;
+    }
+    return small < large ? PrefillTile::Small : PrefillTile::Large;
+}
 
 bool linear_prefill_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus)
 {
@@ -468,32 +501,25 @@ bool linear_prefill_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tok
     const int64_t tiles = ((rows + 63) / 64) * ((n_tokens + 63) / 64);
     if (G != 128 || n_tokens <= 16 || cols > 65536 || tiles >= (1ll << 31)) return false;
     if (n_tokens >= kPrefillMinTokens) return true;
-    // Fewer tokens: the general kernel makes a pass per
-    // 16 tokens, each a round per 16 rows and compute unit, here one or more
-    // rounds of 64 x 64 tiles, two to a compute unit. Both in tenths of a
-    // microsecond per 4096 inputs, at 1 / 2 stages: a general round 29 / 51,
-    // the tiles 318 / 378 with one per compute unit, with two 480 / 560 (two
-    // token tiles that share their codes) or 440 / 540 (two row tiles), and
-    // 620 / 760 for 128 x 128 tiles. Measured, general against this form:
-    // 12288 x 4096, 2 stages, 20 / 48 / 64 / 100 tokens 35 / 49 / 62 / 101
-    // against 38 / 38 / 38 / 53 us, 1 stage, 48 / 64 / 100 tokens 28 / 37 / 59
-    // against 32 / 32 / 42; 25600 x 5120, 2 stages, 48 / 100 tokens 132 / 285
-    // against 67 / 98; 5120 x 5120, 2 stages, 48 / 100 tokens 39 / 81 against
-    // 45 / 45; 4096 x 12288, 64 tokens, 60 against 102.
-    // At 3 / 4 stages the tiles take 446 / 505, 646 / 782, 730 / 1024 and
-    // 1025 / 1426, and the split form's shapes are the other side as well:
-    // 12288 x 4096, 48 / 64 tokens 60 / 66 and 74 / 74 against 45 / 45 and 51 /
-    // 52 us; 5120 x 5120, 64 / 100 tokens, 4 stages, 46 / 86 against 60 / 61;
-    // 4096 x 12288, 120 tokens, 4 stages, 100 against 138.
-    static constexpr int kTiles[4][4] = {{318, 378, 446, 505}, {480, 560, 646, 782},
-                                         {440, 540, 730, 1024}, {620, 760, 1025, 1426}};
+    // Fewer tokens: where the tile that would run costs less than the general
+    // kernel's passes of 16 tokens and, at 3 and 4 stages, a tenth less than
+    // the split form, whose results are the more accurate ones.
+    // Measured, general against this form: 12288 x 4096, 2 stages, 20 / 48 /
+    // 64 / 100 tokens 35 / 49 / 62 / 101 against 38 / 38 / 38 / 53 us, 1 stage,
+    // 48 / 64 / 100 tokens 28 / 37 / 59 against 32 / 32 / 42; 16448 x 2048, 2
+    // stages, 80 tokens 70 against 40; 5120 x 5120, 2 stages, 48 / 100 tokens
+    // 39 / 81 against 45 / 45. The split form against this one: 12288 x 4096, 48
+    // tokens, 3 / 4 stages 45 / 51 against 45 / 51; 12288 x 4096, 128 tokens 73 /
+    // 83 against 66 / 79; 33000 x 2048, 80 tokens 122 / 112 against 85 / 106;
+    // 4096 x 4096, 64 tokens 22 / 24 against 43 / 48.
+    int64_t cost;
+    prefill_tile(rows, n_tokens, k, cus, &cost);
     int64_t other = general_cost(rows, n_tokens, G, k, cus);
     if (k > 2) {
         const int64_t split = split_cost(rows, n_tokens, k, cus);
-        other = split < other ? split : other;
+        other = split < other ? split - split / 10 : other;
     }
-    const int shape = tiles <= cus ? 0 : (rows + 63) / 64 <= cus ? 1 : n_tokens <= 64 ? 2 : 3;
-    return (tiles + 2 * cus - 1) / (2 * cus) * kTiles[shape][k - 1] < other;
+    return cost < other;
 }
 
 hipError_t launch_linear_prefill(const uint32_t *codes, const void *scales, const float *zeros,

@@ -1,0 +1,54 @@
+"""The linear layer's rules for which kernel and tile serve a call, called on
+the CPU through the library's internal functions (256 compute units)."""
+
+import ctypes
+
+import pytest
+
+import paper_2608_04048_amd as rrq
+
+CUS = 256
+I64, I32 = ctypes.c_int64, ctypes.c_int
+SMALL, LARGE, WIDE = range(3)
+
+
+def _function(name, *args, restype=ctypes.c_bool):
+    f = getattr(rrq.load_library(), name)
+    f.argtypes, f.restype = args, restype
+    return f
+
+
+def prefill_fits(rows, cols, k, tokens, G=128):
+    f = _function("_ZN10rrq_detail19linear_prefill_fitsElliili", I64, I64, I32, I32, I64, I32)
+    return f(rows, cols, G, k, tokens, CUS)
+
+
+def prefill_tile(rows, tokens, k):
+    f = _function("_ZN10rrq_detail12prefill_tileElliiPl", I64, I64, I32, I32,
+                  ctypes.POINTER(I64), restype=I32)
+    cost = I64(-1)
+    return f(rows, tokens, k, CUS, ctypes.byref(cost)), cost.value
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+@pytest.mark.parametrize("tokens", [80, 127])
+def test_prefill_rule_charges_the_tile_that_runs(k, tokens):
+    """One more row tile than compute units: the cost stays between one round
+    of the cheaper tile and two, and one and two stages stay with the form."""
+    _, full = prefill_tile(16384, tokens, k)
+    _, more = prefill_tile(16448, tokens, k)
+    _, large = prefill_tile(32768, tokens, k)      # one round of 128 x 128 tiles
+    assert full <= more <= min(2 * full, large)
+    if k <= 2:
+        assert prefill_fits(16384, 2048, k, tokens) and prefill_fits(16448, 2048, k, tokens)
+
+
+@pytest.mark.parametrize("rows", [65281, 70000, 100000, 152064])
+def test_prefill_few_tokens_take_no_padded_tile(rows):
+    """Up to 64 tokens the 128-token tiles would be half padding; above,
+    one-stage calls on so many rows take the wide one."""
+    for tokens in (17, 48, 64):
+        for k in (1, 2, 3, 4):
+            assert prefill_tile(rows, tokens, k)[0] == SMALL
+    assert prefill_tile(rows, 100, 1)[0] == WIDE
+    assert prefill_tile(rows, 128, 1)[0] == WIDE

@@ -4,7 +4,7 @@ integer zero-points and small-integer activations make every intermediate
 exactly representable, so the sampled outputs must equal the exact value bit
 for bit. Shapes on both sides of the rule that picks the form (256 compute
 units): one 64 x 64 tile per compute unit, two that share their codes, two row
-tiles, more than one round, ragged rows and tokens; and a row or token that is
+tiles, more than one round, 128- and 256-row tiles, ragged rows and tokens; and a row or token that is
 not finite stays by itself."""
 
 import numpy as np
@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("rows,cols,M", [
     (12288, 256, 48), (12290, 128, 64), (8200, 384, 65), (8190, 256, 64), (5121, 640, 100),
     (16385, 128, 40), (16384, 256, 127), (25600, 128, 33), (25601, 256, 64), (33000, 128, 127),
+    # 128 x 128 tiles in one round; 256 x 128 at one stage, and not for half a tile of tokens
+    (16448, 256, 80), (24448, 128, 127), (65537, 128, 100), (65537, 128, 48),
     # the general kernel's side
     (12288, 128, 17), (4096, 384, 64), (300, 1152, 100),
 ])
