@@ -633,10 +633,19 @@ bool linear_decode_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_toke
         // same place (8 tokens, 4 / 2 stages: 25600 x 5120 89.5 -> 54.6 us at
         // 4; 5120 x 5120 26.3 / 16.0 -> 16.0 / 11.5; 1024 x 5120 11.6 / 8.3
         // -> 7.3 / 6.8; 4096 x 8192 22.0 -> 18.0 at 4, 13.6 against 13.9 at 2;
-        // 2048 x 1024 5.1 against 5.4 at 4), but for the rows the batch form
-        // takes, where that is ahead or even (12288 x 3072: 18.8 / 12.7 against
-        // 20.0 / 14.6).
-        if (n_tokens > 4 && cols >= 2048 && cols <= 4096) return false;
+        // 2048 x 1024 5.1 against 5.4 at 4), but for rows of 2048 to 4096
+        // inputs. There the batch form has the packages it takes (ahead or
+        // even: 12288 x 3072 18.8 / 12.7 against 20.0 / 14.6), and of the
+        // smaller ones the general kernel those of 1025 to 4096 rows, up to
+        // 2048 rows at 2 and 3 stages only (8 tokens, 4 / 3 / 2 stages, general
+        // against this form: 1024 x 3072 8.3 / 7.1 / 5.9 against 6.2 / 5.9 /
+        // 5.7 us, 2048 x 2560 8.3 / 7.2 / 6.3 against 7.5 / 7.2 / 7.0, 3000 x
+        // 2560 8.7 / 7.5 / 6.5 against 10.7 / 8.6 / 8.4, 5120 x 2048 12.5 / 10.6 /
+        // 9.1 against 9.3 / 8.6 / 8.2; 1024 x 2048, 2 stages, 4.95 against 5.04).
+        if (n_tokens > 4 && cols >= 2048 && cols <= 4096) {
+            if (linear_batch_fits(rows, cols, G, k, n_tokens)) return false;
+            return rows > 4096 || (rows <= 1024 && (k > 2 || cols > 2048)) || (rows <= 2048 && k > 3);
+        }
         if (rows > 4096) return true;
         if (k >= 3) return cols > 1024;
         return cols > 12800 || (rows <= 1024 && cols > 4096);

@@ -23,6 +23,16 @@ def prefill_fits(rows, cols, k, tokens, G=128):
     return f(rows, cols, G, k, tokens, CUS)
 
 
+def decode_fits(rows, cols, k, tokens, G=128):
+    f = _function("_ZN10rrq_detail18linear_decode_fitsElliil", I64, I64, I32, I32, I64)
+    return f(rows, cols, G, k, tokens)
+
+
+def batch_fits(rows, cols, k, tokens, G=128):
+    f = _function("_ZN10rrq_detail17linear_batch_fitsElliil", I64, I64, I32, I32, I64)
+    return f(rows, cols, G, k, tokens)
+
+
 def prefill_tile(rows, tokens, k):
     f = _function("_ZN10rrq_detail12prefill_tileElliiPl", I64, I64, I32, I32,
                   ctypes.POINTER(I64), restype=I32)
@@ -52,3 +62,16 @@ def test_prefill_few_tokens_take_no_padded_tile(rows):
             assert prefill_tile(rows, tokens, k)[0] == SMALL
     assert prefill_tile(rows, 100, 1)[0] == WIDE
     assert prefill_tile(rows, 128, 1)[0] == WIDE
+
+
+def test_decode_rule_leaves_the_batch_form_only_what_it_takes():
+    """5 to 8 tokens on rows of 2048 to 4096 inputs: small packages, which the
+    batch form does not take, go to the decode form where it is ahead."""
+    for tokens in (5, 8):
+        for rows, cols, k in ((1024, 3072, 4), (512, 2048, 3), (1000, 2560, 2), (2048, 2560, 4),
+                              (5120, 2048, 4), (5120, 2048, 2)):
+            assert not batch_fits(rows, cols, k, tokens)
+            assert decode_fits(rows, cols, k, tokens), (rows, cols, k)
+        for rows, cols, k in ((3000, 2560, 4), (2048, 2560, 3), (1024, 2048, 2), (4096, 3968, 4),
+                              (12288, 3072, 3)):
+            assert not decode_fits(rows, cols, k, tokens), (rows, cols, k)

@@ -40,6 +40,8 @@ def _package(rows, cols, M, seed):
     # 5 to 8 tokens, up to 12288 inputs; their edges
     (5000, 128, 8), (4097, 640, 5), (1025, 1152, 6), (1024, 5120, 8), (5121, 5888, 7), (516, 6272, 8),
     (1027, 8192, 5), (1022, 12288, 8), (300, 12416, 6), (1030, 1920, 8), (1030, 2048, 7),
+    # between the batch form and the general kernel
+    (1024, 3072, 8), (1025, 3072, 5), (2047, 2688, 6), (2049, 3968, 7), (5117, 2048, 8), (5117, 2432, 5),
     (4096, 640, 2), (2049, 1024, 1), (2049, 1152, 1), (67, 30848, 2), (1025, 12800, 1),
 ])
 @pytest.mark.parametrize("k", [1, 2, 3, 4])
