@@ -16,6 +16,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+from functools import partial
 from typing import Optional, Tuple
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -295,9 +296,11 @@ def construct(W, group_size: int = 128, n_stages: int = 4, stream=None, out=None
     rows, cols = (W.shape[0], W.shape[1]) if W.dim() == 2 else (1, W.numel())
     n = rows * cols
     if out is None:
-        codes = W.new_empty((n_stages, n // 16), dtype=torch.int32)
-        scales = W.new_empty((n_stages, n // group_size), dtype=torch.float32)
-        zeros = W.new_empty((n_stages, n // group_size), dtype=torch.float32)
+        # (a subclass's new_empty would give another of it)
+        empty = W.new_empty if type(W) is torch.Tensor else partial(torch.empty, device=W.device)
+        codes = empty((n_stages, n // 16), dtype=torch.int32)
+        scales = empty((n_stages, n // group_size), dtype=torch.float32)
+        zeros = empty((n_stages, n // group_size), dtype=torch.float32)
     else:
         codes, scales, zeros = out
     rrq_construct(W, rows, cols, group_size, n_stages, codes, scales, zeros, stream)
@@ -346,7 +349,8 @@ def linear(X, codes, scales, zeros, rows: int, cols: int, group_size: int, k_sta
     _check_device_tensor(X, "X", torch.bfloat16)
     n_tokens = X.numel() // cols
     if out is None:
-        out = X.new_empty((n_tokens, rows), dtype=torch.float32)
+        empty = X.new_empty if type(X) is torch.Tensor else partial(torch.empty, device=X.device)
+        out = empty((n_tokens, rows), dtype=torch.float32)
     rrq_linear(codes, scales, zeros, rows, cols, group_size, codes.shape[0], k_stages, X,
                n_tokens, out, stream)
     return out

@@ -194,3 +194,25 @@ def test_graph_replay_matches_eager(gpu):
         gpu.rrq_linear(c_d, s_d, z_d, rows, cols, G, S, 1 + i % 3, X, 2, Y_eager[:2])
         gpu.rrq_linear(c_d, s_d, z_d, rows, cols, G, S, 3, X, 3, Y_eager)
         torch.cuda.synchronize()
+
+
+def test_outputs_are_plain_tensors(gpu):
+    """construct and linear return plain tensors for inputs of a subclass or
+    parameters, with the values of plain inputs."""
+    import torch
+
+    class Named(torch.Tensor):
+        pass
+
+    rows, cols = 64, 256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    W = torch.randn((rows, cols), generator=g, device="cuda").bfloat16()
+    X = torch.randn((3, cols), generator=g, device="cuda").bfloat16()
+    package = gpu.construct(W, 128, 2)
+    want = gpu.linear(X, *package, rows, cols, 128, 2)
+    for wrap in (lambda t: t.as_subclass(Named), lambda t: torch.nn.Parameter(t, requires_grad=False)):
+        again = gpu.construct(wrap(W), 128, 2)
+        y = gpu.linear(wrap(X), *package, rows, cols, 128, 2)
+        assert all(type(t) is torch.Tensor for t in (*again, y))
+        assert torch.equal(y, want) and all(torch.equal(a, b) for a, b in zip(again, package))
