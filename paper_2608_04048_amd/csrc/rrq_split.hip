@@ -544,10 +544,15 @@ hipError_t launch_g(const Call &c, Shape s)
 
 }  // namespace
 
+int split_shape(int64_t rows, int64_t n_tokens, int k, int cus, int64_t *cost)
+{
+    return cheapest(rows, n_tokens, k, cus, cost);
+}
+
 int64_t split_cost(int64_t rows, int64_t n_tokens, int k, int cus)
 {
     int64_t cost;
-    cheapest(rows, n_tokens, k, cus, &cost);
+    split_shape(rows, n_tokens, k, cus, &cost);
     return cost;
 }
 

@@ -1,5 +1,6 @@
 """The linear layer's rules for which kernel and tile serve a call, called on
-the CPU through the library's internal functions (256 compute units)."""
+the CPU through the library's internal functions (256 compute units). form()
+tells the other tests which kernel they run."""
 
 import ctypes
 
@@ -31,6 +32,26 @@ def decode_fits(rows, cols, k, tokens, G=128):
 def batch_fits(rows, cols, k, tokens, G=128):
     f = _function("_ZN10rrq_detail17linear_batch_fitsElliil", I64, I64, I32, I32, I64)
     return f(rows, cols, G, k, tokens)
+
+
+def split_fits(rows, cols, k, tokens, G=128):
+    f = _function("_ZN10rrq_detail17linear_split_fitsElliili", I64, I64, I32, I32, I64, I32)
+    return f(rows, cols, G, k, tokens, CUS)
+
+
+def split_shape(rows, tokens, k):
+    f = _function("_ZN10rrq_detail11split_shapeElliiPl", I64, I64, I32, I32,
+                  ctypes.POINTER(I64), restype=I32)
+    return "ABCDEF"[f(rows, tokens, k, CUS, ctypes.byref(I64()))]
+
+
+def form(rows, cols, k, tokens, G=128):
+    """The kernel that serves a call (the order of the C ABI's dispatch)."""
+    for name, fits in (("decode", decode_fits), ("batch", batch_fits), ("split", split_fits),
+                       ("prefill", prefill_fits)):
+        if fits(rows, cols, k, tokens, G):
+            return name
+    return "general"
 
 
 def prefill_tile(rows, tokens, k):
@@ -75,3 +96,21 @@ def test_decode_rule_leaves_the_batch_form_only_what_it_takes():
         for rows, cols, k in ((3000, 2560, 4), (2048, 2560, 3), (1024, 2048, 2), (4096, 3968, 4),
                               (12288, 3072, 3)):
             assert not decode_fits(rows, cols, k, tokens), (rows, cols, k)
+
+
+def test_split_tests_reach_every_tile_shape():
+    from test_gpu_split import EXACT
+    seen = {(G, split_shape(rows, M, k)) for rows, cols, G, M in EXACT for k in (1, 2, 3, 4)
+            if form(rows, cols, k, M, G) == "split"}
+    assert seen == {(G, s) for G in (32, 64, 128) for s in "ABCDEF"}
+
+
+def test_prefill_tests_run_the_prefill_form():
+    import test_gpu_prefill as t
+    for rows, cols, M in (*t.EXACT, *t.LARGE):
+        assert all(form(rows, cols, k, M) == "prefill" for k in (1, 2, 3, 4)), (rows, cols, M)
+    rows, cols, M = t.WIDE
+    assert form(rows, cols, 1, M) == "prefill" and prefill_tile(rows, M, 1)[0] == WIDE
+    for rows, cols, M, k in t.SAME_ORDER:
+        assert form(rows, cols, k, M) == "prefill"
+        assert all(form(rows, cols, k, min(32, M - m)) == "general" for m in range(0, M, 32))

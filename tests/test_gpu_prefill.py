@@ -1,5 +1,6 @@
-"""GPU parity of rrq_linear's prefill form (groups of 128, at least 128 tokens),
-through the C ABI:
+"""GPU parity of rrq_linear's prefill form (groups of 128, at least 128 tokens;
+with 3 and 4 stages where the split form does not take them), through the C
+ABI:
 
 * exact: power-of-two scales, integer or dyadic zero-points and
   small-integer activations make every intermediate exactly representable,
@@ -56,12 +57,15 @@ def _exact(rows, cols, M, seed):
     return codes, s, z, xb
 
 
-@pytest.mark.parametrize("rows,cols,M", [
+EXACT = [
     (16, 128, 128), (5, 384, 140), (64, 1024, 192), (100, 4096, 129), (257, 2048, 130),
     (64, 12288, 200), (1, 4224, 161),
     # from 1024 tokens the 2-4 stage kernels raise their MFMA stretches' priority
     (70, 1024, 1100), (33, 2048, 1024),
-])
+]
+
+
+@pytest.mark.parametrize("rows,cols,M", EXACT)
 @pytest.mark.parametrize("k", [1, 2, 3, 4])
 def test_prefill_exact(gpu, rows, cols, M, k):
     _log(f"prefill exact rows={rows} cols={cols} M={M} k={k}")
@@ -179,15 +183,16 @@ def _realistic(rows, cols, seed, zp="int", sd="f32"):
     return oc, os_, oz
 
 
-@pytest.mark.parametrize("rows,cols,M,k", [(300, 4096, 160, 4), (64, 12288, 152, 2),
-                                           (129, 1024, 250, 1), (100, 2048, 1056, 3),
-                                           (1990, 1024, 1504, 4), (1990, 1024, 1504, 2),
-                                           (3000, 384, 2720, 1)])
+SAME_ORDER = [(300, 4096, 160, 4), (64, 12288, 152, 2), (129, 1024, 250, 1), (100, 2048, 1056, 3),
+              (1990, 1024, 1504, 4), (1990, 1024, 1504, 2), (3000, 384, 2720, 1)]
+
+
+@pytest.mark.parametrize("rows,cols,M,k", SAME_ORDER)
 def test_prefill_equals_16_token_calls(gpu, rows, cols, M, k):
     """The prefill form and the general kernel's 16-token tiles accumulate
     every output in the same order: identical bits on a realistic package.
     The reference calls take 32 tokens at a time (the last one fewer but more
-    than 16), a count that only the general kernel serves."""
+    than 16), which the general kernel serves on so few rows."""
     _log(f"prefill vs 16-token calls rows={rows} cols={cols} M={M} k={k}")
     oc, os_, oz = _realistic(rows, cols, rows + M)
     rng = np.random.default_rng(M)
@@ -228,8 +233,8 @@ def test_prefill_realistic_within_bound(gpu, zp, sd):
 def test_prefill_full_size_sampled(gpu, rows, cols, k):
     """The benchmark's prefill sizes (2048 tokens on the Qwen3-8B q/o,
     gate/up and down shapes at 1 and 4 stages, the launch configurations the
-    bench times) on an exact package: sampled rows,
-    every token, bit-exact."""
+    bench times; at 4 stages they take the split form) on an exact package:
+    sampled rows, every token, bit-exact."""
     M = 2048
     _log(f"prefill full size rows={rows} cols={cols} M={M} k={k}")
     codes, s, z, xb = _exact(rows, cols, M, rows + k)

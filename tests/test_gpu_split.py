@@ -28,6 +28,7 @@ import pytest
 
 import oracle
 from oracle import rrq_oracle as npo
+from test_dispatch import form
 
 pytestmark = pytest.mark.gpu
 U = 2.0 ** -24
@@ -71,15 +72,20 @@ def _sample(rows, seed):
 
 # On 256 compute units: 256-, 128- and 64-token tiles of 128 rows for 4090
 # rows at 2043, 1021 and 490 tokens, a quarter per wave with 64-, 32- and
-# 32-token tiles of 32, 32 and 64 rows for 4090 rows at 121 tokens (groups of
-# 64), 250 rows, and 4090 rows at 121 tokens (groups of 32). Rows of 1 to 9
-# chunks of 128 inputs, partial last chunks with the smaller groups.
-@pytest.mark.parametrize("rows,cols,G,M", [
+# 32-token tiles of 32, 32 and 64 rows for 4090 rows at 121 tokens, 250 or
+# fewer rows, and 12290 rows at 30 tokens. Rows of 1 to 9 chunks of 128 inputs,
+# partial last chunks with the smaller groups.
+EXACT = [
     (4090, 320, 64, 2043), (4090, 448, 64, 1021), (4090, 64, 64, 490), (4090, 576, 64, 121),
     (250, 1088, 64, 140), (4090, 608, 32, 1021), (4090, 32, 32, 490), (4090, 1120, 32, 121),
     (35, 96, 32, 67), (1, 32, 32, 130), (4090, 384, 128, 2043), (4090, 1152, 128, 1021),
     (4090, 128, 128, 1021), (1023, 640, 128, 127), (70, 128, 128, 66),
-])
+    (4090, 352, 32, 2043), (12290, 160, 32, 30), (12290, 192, 64, 30), (12290, 128, 128, 30),
+    (16700, 128, 128, 50), (4090, 256, 128, 100),
+]
+
+
+@pytest.mark.parametrize("rows,cols,G,M", EXACT)
 @pytest.mark.parametrize("k", [1, 2, 3, 4])
 def test_split_exact(gpu, rows, cols, G, M, k):
     if G == 128 and k < 3:
@@ -197,9 +203,9 @@ def test_split_extreme_token(gpu, value):
         assert np.all(np.abs(y[7].astype(np.float64) - ref[7]) <= tol[7])
 
 
-# Which waves take a row's chunks: each quarter its own (40 and 72 tokens, 300
+# Which waves take a row's chunks: each quarter its own (60 and 72 tokens, 300
 # rows) or all in turn (1000 tokens, 4090 rows).
-_SPLITS = [(300, 40), (300, 72), (4090, 1000)]
+_SPLITS = [(300, 60), (300, 72), (4090, 1000)]
 
 
 def _ranged(rows, cols, G, M, fx, fs, seed):
@@ -216,6 +222,7 @@ def _ranged(rows, cols, G, M, fx, fs, seed):
 
 
 def _check_bound(gpu, codes, s, z, rows, cols, G, k, xb, what):
+    assert form(rows, cols, k, xb.size // cols, G) == "split"
     idx = _sample(rows, 1)
     y = _run(gpu, codes, s, z, rows, cols, G, k, xb)
     ref = npo.linear(codes, s, z, rows, cols, G, k, xb, row_index=idx)
@@ -291,6 +298,7 @@ def test_split_token_does_not_depend_on_the_others(gpu, G, R):
     other tokens of its tile do as it does, or not, and wherever it stands."""
     rows, cols, M, k = 300, 2048, 72, 4
     chunk = np.where(np.arange(16) % 4 == 0, 2.0 ** R, 1.0)
+    assert form(rows, cols, k, M, G) == "split"
     codes, s, z, xb = _ranged(rows, cols, G, M, np.repeat(chunk, 128), np.repeat(1 / chunk, 128 // G), 3)
     y = _run(gpu, codes, s, z, rows, cols, G, k, xb)
     rng = np.random.default_rng(4)
@@ -302,3 +310,22 @@ def test_split_token_does_not_depend_on_the_others(gpu, G, R):
         mixed[at] = xb.reshape(M, cols)[17]
         ym = _run(gpu, codes, s, z, rows, cols, G, k, mixed.reshape(-1))
         assert np.array_equal(ym[at].view(np.uint32), y[17].view(np.uint32)), at
+
+
+@pytest.mark.parametrize("rows,cols,G,M,k", [(300, 1088, 64, 40, 2), (4090, 384, 128, 1021, 4)])
+def test_split_graph_replays(gpu, rows, cols, G, M, k):
+    import torch
+    assert form(rows, cols, k, M, G) == "split"
+    codes, s, z, xb = _exact(rows, cols, G, M, 7)
+    want = _run(gpu, codes, s, z, rows, cols, G, k, xb)
+    c, sc, ze = (torch.from_numpy(a).cuda() for a in (codes.view(np.int32).copy(), s, z))
+    X = torch.from_numpy(xb.view(np.int16).reshape(M, cols).copy()).cuda().view(torch.bfloat16)
+    Y = torch.empty((M, rows), device="cuda")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        gpu.linear(X, c, sc, ze, rows, cols, G, k, out=Y)
+    for _ in range(3):
+        Y.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(Y.cpu().numpy().view(np.uint32), want.view(np.uint32))
