@@ -76,7 +76,10 @@ __device__ __forceinline__ f32x4 mfma(const u32x4 &a, const u32x4 &b, const f32x
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Entry g of a lane's four C rows.
+// Entry g of a lane's four C rows. (The fixed shapes for up to 8 tokens write
+// it out: after a call the compiler schedules their loop differently, 4096 x
+// 8192, 4 tokens, 4 stages 14.8 -> 15.4 us, 24576 x 4096, 1 token 28.5 -> 28.9; for
+// 9 to 16 tokens it is the other way, 1024 x 4096, 16 tokens 8.6 -> 8.3.)
 __device__ __forceinline__ float diagonal(const f32x4 &c, uint32_t g)
 {
     return g == 0 ? c[0] : g == 1 ? c[1] : g == 2 ? c[2] : c[3];
@@ -360,8 +363,27 @@ __global__ __launch_bounds__(64 * WV, ANY ? any_budget(K, SPW, TQ, DEF)
     // sets; operand set u = TQ set + q), then the ring.
     const uint32_t ga = n & 3;
     u32x4 run[SPW * TQ][4];
-    auto load_runs = [&]() {
+    if constexpr (!ANY) {
         const u32x4 xs = make_desc(X, (uint32_t)n_tokens * (uint32_t)cols * 2);
+#pragma unroll
+        for (int s = 0; s < SPW; ++s)
+#pragma unroll
+            for (int q = 0; q < TQ; ++q) {
+                const int t = 4 * q + (n >> 2);
+                const uint32_t ta = (uint32_t)(t < n_tokens ? t : n_tokens - 1);
+                const uint32_t gi = ((uint32_t)wave * SPW + s) * 4 + ga;
+                const uint32_t off = ta * (uint32_t)cols * 2 + gi * 256 + 64 * (uint32_t)j;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) run[TQ * s + q][i] = load_run(xs, off + 16 * i);
+            }
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d) issue_next();
+    if constexpr (ANY) {
+        // up to 20 runs, loaded behind the ring, which lands with them: the
+        // compiler's own wait costs nothing there
+        const auto xs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<uint16_t *>(X), 0, (int)((uint32_t)n_tokens * (uint32_t)cols * 2), kRsrcWord3);
 #pragma unroll
         for (int s = 0; s < SPW; ++s)
 #pragma unroll
@@ -370,27 +392,14 @@ __global__ __launch_bounds__(64 * WV, ANY ? any_budget(K, SPW, TQ, DEF)
                 const uint32_t ta = (uint32_t)(t < n_tokens ? t : n_tokens - 1);
                 const uint32_t gi = (set0 + s) * 4 + ga;
                 uint32_t off = ta * (uint32_t)cols * 2 + gi * 256 + 64 * (uint32_t)j;
-                if (ANY && (s >= my_sets || gi >= gpr)) off = kSkip;
+                if (s >= my_sets || gi >= gpr) off = kSkip;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if constexpr (ANY)
-                        run[TQ * s + q][i] = __builtin_amdgcn_raw_buffer_load_b128(
-                            __builtin_amdgcn_make_buffer_rsrc(
-                                const_cast<uint16_t *>(X), 0,
-                                (int)((uint32_t)n_tokens * (uint32_t)cols * 2), kRsrcWord3),
-                            off + 16 * i, 0, 0);
-                    else
-                        run[TQ * s + q][i] = load_run(xs, off + 16 * i);
-                }
+                for (int i = 0; i < 4; ++i)
+                    run[TQ * s + q][i] = __builtin_amdgcn_raw_buffer_load_b128(xs, off + 16 * i, 0, 0);
             }
-    };
-    if constexpr (!ANY) load_runs();
-#pragma unroll
-    for (int d = 0; d < D; ++d) issue_next();
-    // (ANY: up to 20 runs, loaded behind the ring, which lands with them: the
-    // compiler's own wait costs nothing there)
-    if constexpr (ANY) load_runs();
-    else wait_runs<D * L::DMA>(run);
+    } else {
+        wait_runs<D * L::DMA>(run);
+    }
 
     u32x4 a[SPW * TQ][4];
     float sxd[SPW * TQ];
@@ -404,7 +413,8 @@ __global__ __launch_bounds__(64 * WV, ANY ? any_budget(K, SPW, TQ, DEF)
 #pragma unroll
             for (int b = 0; b < 4; ++b) acc = mfma(a[s][b], ones, acc);
             // the lane's diagonal entry (token j, group gb) is the one used
-            sxd[s] = diagonal(acc, gb);
+            if constexpr (ANY || TQ == 4) sxd[s] = diagonal(acc, gb);
+            else sxd[s] = gb == 0 ? acc[0] : gb == 1 ? acc[1] : gb == 2 ? acc[2] : acc[3];
         }
     }
 
@@ -474,7 +484,10 @@ __global__ __launch_bounds__(64 * WV, ANY ? any_budget(K, SPW, TQ, DEF)
         // groups of the lanes n = 4 r .. 4 r + 3, kept for the batch reduction
 #pragma unroll
         for (int q = 0; q < TQ; ++q) {
-            float y = ANY ? acc[q][0] : diagonal(acc[q], gb);
+            float y;
+            if constexpr (ANY) y = acc[q][0];
+            else if constexpr (TQ == 4) y = diagonal(acc[q], gb);
+            else y = gb == 0 ? acc[q][0] : gb == 1 ? acc[q][1] : gb == 2 ? acc[q][2] : acc[q][3];
             if constexpr (!ANY) {
 #pragma unroll
                 for (int set = 0; set < SPW; ++set) y = __builtin_fmaf(-c[set], sxd[TQ * set + q], y);
