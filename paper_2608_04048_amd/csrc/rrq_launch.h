@@ -101,8 +101,9 @@ hipError_t launch_linear_prefill(const uint32_t *codes, const void *scales, cons
 // The tile shape a call of this form takes (0 to 5: A to F of rrq_split.hip),
 // its time, and the general kernel's with more than 16 tokens, in tenths of a
 // microsecond per 4096 inputs.
-int split_shape(int64_t rows, int64_t n_tokens, int k, int cus, int64_t *cost);
-int64_t split_cost(int64_t rows, int64_t n_tokens, int k, int cus);
+int split_shape(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus,
+                int64_t *cost);
+int64_t split_cost(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus);
 int64_t general_cost(int64_t rows, int64_t n_tokens, int G, int k, int cus);
 bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus);
 hipError_t launch_linear_split(const uint32_t *codes, const void *scales, const float *zeros,

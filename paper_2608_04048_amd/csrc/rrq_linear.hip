@@ -484,8 +484,8 @@ int64_t general_cost(int64_t rows, int64_t n_tokens, int G, int k, int cus)
     // HBM: e.g. 64 tokens, groups of 128, 4 stages 33.5 / 64.3 / 93.0 us,
     // groups of 64, 2 stages 29.4 / 42.2 / 62.9, groups of 32, 1 stage 33.6 /
     // 39.6 / 57.4.
-    static constexpr int kPass[3][4] = {{60, 22, 0, 0}, {50, 38, 42, 26}, {0, 0, 0, 10}};
-    static constexpr int kRound[3][4] = {{33, 94, 165, 205}, {17, 45, 62, 102}, {29, 51, 70, 86}};
+    static constexpr int kPass[3][4] = {{60, 22, 0, 0}, {50, 28, 21, 20}, {0, 0, 0, 10}};
+    static constexpr int kRound[3][4] = {{33, 94, 165, 205}, {17, 51, 77, 112}, {29, 51, 70, 86}};
     const int64_t passes = (n_tokens + 15) / 16;
     const int64_t rounds = ((rows + 15) / 16 + cus - 1) / cus;
     const int g = G == 32 ? 0 : G == 64 ? 1 : 2;

@@ -503,7 +503,8 @@ bool linear_prefill_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tok
     if (n_tokens >= kPrefillMinTokens) return true;
     // Fewer tokens: where the tile that would run costs less than the general
     // kernel's passes of 16 tokens and, at 3 and 4 stages, a tenth less than
-    // the split form, whose results are the more accurate ones.
+    // the split form, whose results are the more accurate ones (a quarter less
+    // with two row tiles per compute unit and up to 64 tokens).
     // Measured, general against this form: 12288 x 4096, 2 stages, 20 / 48 /
     // 64 / 100 tokens 35 / 49 / 62 / 101 against 38 / 38 / 38 / 53 us, 1 stage,
     // 48 / 64 / 100 tokens 28 / 37 / 59 against 32 / 32 / 42; 16448 x 2048, 2
@@ -516,8 +517,9 @@ bool linear_prefill_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_tok
     prefill_tile(rows, n_tokens, k, cus, &cost);
     int64_t other = general_cost(rows, n_tokens, G, k, cus);
     if (k > 2) {
-        const int64_t split = split_cost(rows, n_tokens, k, cus);
-        other = split < other ? split - split / 10 : other;
+        const int64_t split = split_cost(rows, cols, G, k, n_tokens, cus);
+        const int64_t part = n_tokens <= 64 && rows > 64 * (int64_t)cus ? 4 : 10;
+        other = split < other ? split - split / part : other;
     }
     return cost < other;
 }

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
     const uint32_t *__restrict__ codes, const char *__restrict__ scales,
     const float *__restrict__ zeros, int64_t rows, int64_t cols, int64_t plane_words,
     int64_t plane_groups, const uint16_t *__restrict__ X, int64_t n_tokens,
-    float *__restrict__ Y, int zero_point, int scale_type, int row_tiles)
+    float *__restrict__ Y, int zero_point, int scale_type, int row_pitch)
 {
     using L = Tile<K, GPC, WR, WQ, T>;
     constexpr int G = 128 / GPC;
@@ -161,8 +161,9 @@ __global__ __launch_bounds__(64 * WR * WQ, WR * WQ >= 8 ? 2 : 1) void split_kern
     asm volatile("s_mov_b32 %0, 0xbf80" : "=s"(neg_lo));
     asm volatile("s_mov_b32 %0, 0xbf800000" : "=s"(neg_hi));
 
-    const int64_t m0 = (int64_t)(blockIdx.x / row_tiles) * L::TOK;
-    const int64_t o0 = (int64_t)(blockIdx.x % row_tiles) * (16 * WR) + 16 * wr;
+    const int64_t m0 = (int64_t)(blockIdx.x / row_pitch) * L::TOK;
+    const int64_t o_tile = (int64_t)(blockIdx.x % row_pitch) * (16 * WR), o0 = o_tile + 16 * wr;
+    if (o_tile >= rows) return;         // (of the pitch only)
     const uint32_t tokens_here = (uint32_t)(n_tokens - m0 < L::TOK ? n_tokens - m0 : L::TOK);
     const int64_t rem = rows - o0;
     const uint32_t rows_here = rem <= 0 ? 0u : (uint32_t)(rem < 16 ? rem : 16);
@@ -456,6 +457,27 @@ hipError_t launch(void (*kernel)(Args...), int grid, int block, hipStream_t stre
                            argv, 0, stream);
 }
 
+// Tile shapes: A, B, C stage all quarters in turn (8 row waves, 256 / 128 /
+// 64 tokens), D, E, F give each quarter its own waves (32 rows x 64 tokens,
+// 32 x 32, 64 x 32), for calls with too few tiles to fill the chip. A compute
+// unit runs one workgroup, or two of C and, at 1 and 2 stages, of E (LDS), so
+// a call costs its rounds of workgroups times the shape's time per round, with
+// one (kCost) or two (kPair) to a compute unit: in tenths of a microsecond per
+// 4096 inputs by stages, measured with groups of 64 and 128 on 4096 to 16384
+// rows at 64 to 2048 tokens, packages read from HBM.
+enum Shape { A, B, C, D, E, F, kShapes };
+constexpr int kRows[kShapes] = {128, 128, 128, 32, 32, 64};
+constexpr int kTokens[kShapes] = {256, 128, 64, 64, 32, 32};
+constexpr int kCost[4][kShapes] = {{1560, 900, 570, 205, 160, 240}, {1630, 970, 650, 230, 190, 280},
+                                   {1720, 1060, 760, 260, 225, 340}, {1830, 1160, 860, 290, 265, 450}};
+constexpr int kPair[4][kShapes] = {{0, 0, 1030, 0, 250, 0}, {0, 0, 1210, 0, 300, 0},
+                                   {0, 0, 1360, 0, 0, 0}, {0, 0, 1540, 0, 0, 0}};
+
+constexpr Shape shape_of(int wr, int t)
+{
+    return wr == 8 ? (t == 16 ? A : t == 8 ? B : C) : wr == 4 ? F : t == 4 ? D : E;
+}
+
 struct Call {
     const uint32_t *codes;
     const char *scales;
@@ -465,17 +487,29 @@ struct Call {
     const uint16_t *X;
     int64_t n_tokens;
     float *Y;
+    int cus;
     hipStream_t stream;
 };
 
 template <int K, int GPC, int WR, int WQ, int T>
 hipError_t launch_t(const Call &c)
 {
-    const int row_tiles = (int)((c.rows + 16 * WR - 1) / (16 * WR));
-    const int grid = (int)((int64_t)row_tiles * ((c.n_tokens + 16 * T - 1) / (16 * T)));
+    // Workgroups go to the 8 XCDs in turn: with a pitch of a multiple of 8 the
+    // token tiles of a row tile share an XCD, and its L2 the package's lines
+    // (11000 x 4096, 2048 tokens, 4 stages 636 -> 503 us, 16000 x 5120, 100 tokens
+    // 266 -> 117); not where the XCDs that get the rest would need another
+    // round (10699 x 8192, 287 tokens 248 -> 402).
+    const int64_t row_tiles = (c.rows + 16 * WR - 1) / (16 * WR);
+    const int64_t token_tiles = (c.n_tokens + 16 * T - 1) / (16 * T);
+    const int64_t tiles = row_tiles * token_tiles, per_xcd = (row_tiles + 7) / 8 * token_tiles;
+    const int64_t slots = tiles > c.cus && kPair[K - 1][shape_of(WR, T)] ? 2 * c.cus : c.cus;
+    const bool pitched = token_tiles > 1 &&
+                         (per_xcd * 8 + slots - 1) / slots <= (tiles + slots - 1) / slots;
+    const int row_pitch = (int)(pitched ? (row_tiles + 7) / 8 * 8 : row_tiles);
+    const int grid = (int)(row_pitch * token_tiles);
     return launch(split_kernel<K, GPC, WR, WQ, T>, grid, 64 * WR * WQ, c.stream, c.codes,
                   c.scales, c.zeros, c.rows, c.cols, c.rows * c.cols / 16,
-                  c.rows * c.cols * GPC / 128, c.X, c.n_tokens, c.Y, c.zp, c.sdt, row_tiles);
+                  c.rows * c.cols * GPC / 128, c.X, c.n_tokens, c.Y, c.zp, c.sdt, row_pitch);
 }
 
 template <int GPC, int WR, int WQ, int T>
@@ -492,34 +526,38 @@ hipError_t launch_k(const Call &c)
     }
 }
 
-// Tile shapes: A, B, C stage all quarters in turn (8 row waves, 256 / 128 /
-// 64 tokens), D, E, F give each quarter its own waves (32 rows x 64 tokens,
-// 32 x 32, 64 x 32), for calls with too few tiles to fill the chip. A compute
-// unit runs one workgroup, or two of C and, at 1 and 2 stages, of E (LDS), so
-// a call costs its rounds of workgroups times the shape's time per round, with
-// one (kCost) or two (kPair) to a compute unit: in tenths of a microsecond per
-// 4096 inputs by stages, measured with groups of 64 and 128 on 4096 to 16384
-// rows at 64 to 2048 tokens, packages read from HBM.
-enum Shape { A, B, C, D, E, F, kShapes };
-constexpr int kRows[kShapes] = {128, 128, 128, 32, 32, 64};
-constexpr int kTokens[kShapes] = {256, 128, 64, 64, 32, 32};
-constexpr int kCost[4][kShapes] = {{1560, 900, 570, 205, 160, 240}, {1630, 970, 650, 230, 190, 280},
-                                   {1720, 1060, 760, 260, 225, 340}, {1830, 1160, 860, 290, 255, 450}};
-constexpr int kPair[4][kShapes] = {{0, 0, 1030, 0, 250, 0}, {0, 0, 1210, 0, 300, 0},
-                                   {0, 0, 1360, 0, 0, 0}, {0, 0, 1540, 0, 0, 0}};
+// A chunk takes 32 bytes of a row's line of codes and 4 to 16 of its lines of
+// scales and zero-points, per stage, and the rows in flight hold theirs in the
+// L2 (32 MB) until the next chunk. Where they outgrow it every chunk reads them
+// again, which sets the time of C from about 36 MB of lines (one per row and
+// stage and array) and, at 4 stages, of F past 16384 rows: 24 tokens, 4 stages,
+// groups of 128 / 64, 24576 x 4096 C 110 / 116 us, 28672 x 4096 C 172 / 181, F 102 /
+// 149, E 98 / 113. (Rows of up to 2048 inputs share their lines of scales:
+// 24576 x 2048, 48 tokens, 4 stages C 47.5, D 50; with groups of 32 the other
+// shapes lose as much.)
+int64_t shape_cost(int s, int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus)
+{
+    const int64_t row_tiles = (rows + kRows[s] - 1) / kRows[s];
+    const int64_t token_tiles = (n_tokens + kTokens[s] - 1) / kTokens[s];
+    const int64_t tiles = row_tiles * token_tiles, left = tiles % (2 * cus);
+    const int64_t one = kCost[k - 1][s], pair = kPair[k - 1][s];
+    const int64_t c = pair == 0 ? (tiles + cus - 1) / cus * one
+                                : tiles / (2 * cus) * pair + (left == 0 ? 0 : left <= cus ? one : pair);
+    int64_t again = 0;
+    if (cols > 2048 && G > 32 && s == C && (row_tiles < 2 * cus ? row_tiles : 2 * cus) * k > 732)
+        again = rows * k * token_tiles * (G == 128 ? 125 : 150) / 10000;
+    if (cols > 2048 && G > 32 && s == F && k == 4 && rows > 16384)
+        again = rows * k * token_tiles * (G == 128 ? 85 : 120) / 10000;
+    return c > again ? c : again;
+}
 
 // The cheapest shape and its cost (tenths of a microsecond per 4096 inputs).
-Shape cheapest(int64_t rows, int64_t n_tokens, int k, int cus, int64_t *cost)
+Shape cheapest(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus, int64_t *cost)
 {
     Shape best = B;
     *cost = INT64_MAX;
     for (int s = kShapes - 1; s >= 0; --s) {
-        const int64_t tiles = ((rows + kRows[s] - 1) / kRows[s]) *
-                              ((n_tokens + kTokens[s] - 1) / kTokens[s]);
-        const int64_t one = kCost[k - 1][s], pair = kPair[k - 1][s];
-        const int64_t left = tiles % (2 * cus);
-        const int64_t c = pair == 0 ? (tiles + cus - 1) / cus * one
-                                    : tiles / (2 * cus) * pair + (left == 0 ? 0 : left <= cus ? one : pair);
+        const int64_t c = shape_cost(s, rows, cols, G, k, n_tokens, cus);
         if (c < *cost) {
             *cost = c;
             best = (Shape)s;
@@ -544,15 +582,32 @@ hipError_t launch_g(const Call &c, Shape s)
 
 }  // namespace
 
-int split_shape(int64_t rows, int64_t n_tokens, int k, int cus, int64_t *cost)
+int split_shape(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus,
+                int64_t *cost)
 {
-    return cheapest(rows, n_tokens, k, cus, cost);
+    return cheapest(rows, cols, G, k, n_tokens, cus, cost);
 }
 
-int64_t split_cost(int64_t rows, int64_t n_tokens, int k, int cus)
+int64_t split_cost(int64_t rows, int64_t cols, int G, int k, int64_t n_tokens, int cus)
 {
     int64_t cost;
-    split_shape(rows, n_tokens, k, cus, &cost);
+    const int shape = split_shape(rows, cols, G, k, n_tokens, cus, &cost);
+    // The shapes with a quarter per wave read lines again as well, on 8193 to
+    // 16384 rows from about 66 MB of lines (4 quarters' each), 50 MB on rows of
+    // 8192 inputs or more; fitted, 24 tokens: 4 stages, groups of 128, 16384 x
+    // 8192 171 us against 102 without it, 10922 x 12288 189 against 142, 16000 x
+    // 6144 109 against 68; groups of 64, 10885 x 8192 161 against 90, 2 stages,
+    // 16384 x 8192 125 against 56. (The general kernel takes 136, 147, 103, 137
+    // and 91, the prefill form 101, 142 and 79. With smaller groups, 4 stages and
+    // planes a multiple of an XCD's 4 MiB apart it loses as much: 16384 x 8192,
+    // groups of 64, 286 against 250.)
+    const bool aliased = G < 128 && k == 4 && rows * cols % (1 << 24) == 0;
+    if (shape >= D && (rows > 8192 || (rows == 8192 && cols >= 12288)) && rows <= 16384 &&
+        rows * k > (cols < 8192 ? 43000 : 32600) && !aliased) {
+        const int64_t token_tiles = (n_tokens + kTokens[shape] - 1) / kTokens[shape];
+        const int64_t again = rows * k * (75 + cols / 192) * (G == 128 ? 10 : 14) / 100000 * token_tiles;
+        if (again > cost) cost = again;
+    }
     return cost;
 }
 
@@ -560,7 +615,7 @@ bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_token
 {
     // The activation descriptor spans at most 256 rows of X (under 2^31
     // bytes), and the grid fits an int.
-    const int64_t tiles32 = ((rows + 31) / 32) * ((n_tokens + 31) / 32);
+    const int64_t tiles32 = ((rows + 31) / 32 + 7) * ((n_tokens + 31) / 32);
     if (n_tokens <= 16 || cols > 65536 || tiles32 >= (1ll << 31)) return false;
     if (G == 128) {
         if (n_tokens < kPrefillMinTokens && linear_prefill_fits(rows, cols, G, k, n_tokens, cus))
@@ -582,12 +637,7 @@ bool linear_split_fits(int64_t rows, int64_t cols, int G, int k, int64_t n_token
             return 8 * tiles >= (k == 4 ? 7 : 8) * (int64_t)cus;
         }
     }
-    // Against the general kernel. At one stage with groups of 64 that is the
-    // slightly more accurate one on rows of up to 8192 inputs (2048 / 4096
-    // inputs 1.9e-7 / 2.0e-7 against 2.2e-7 / 2.2e-7) and keeps what this form
-    // would not take well under two thirds of the time for.
-    const int64_t general = general_cost(rows, n_tokens, G, k, cus);
-    return split_cost(rows, n_tokens, k, cus) < (G == 64 && k == 1 ? 6 * general / 10 : general);
+    return split_cost(rows, cols, G, k, n_tokens, cus) < general_cost(rows, n_tokens, G, k, cus);
 }
 
 hipError_t launch_linear_split(const uint32_t *codes, const void *scales, const float *zeros,
@@ -596,9 +646,9 @@ hipError_t launch_linear_split(const uint32_t *codes, const void *scales, const 
                                int cus, hipStream_t stream)
 {
     const Call c = {codes, static_cast<const char *>(scales), zeros, rows, cols, k, zero_point,
-                    scale_type, X, n_tokens, Y, stream};
+                    scale_type, X, n_tokens, Y, cus, stream};
     int64_t cost;
-    const Shape shape = cheapest(rows, n_tokens, k, cus, &cost);
+    const Shape shape = cheapest(rows, cols, G, k, n_tokens, cus, &cost);
     switch (G) {
     case 32: return launch_g<4>(c, shape);
     case 64: return launch_g<2>(c, shape);

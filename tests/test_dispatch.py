@@ -39,10 +39,10 @@ def split_fits(rows, cols, k, tokens, G=128):
     return f(rows, cols, G, k, tokens, CUS)
 
 
-def split_shape(rows, tokens, k):
-    f = _function("_ZN10rrq_detail11split_shapeElliiPl", I64, I64, I32, I32,
+def split_shape(rows, cols, tokens, k, G=128):
+    f = _function("_ZN10rrq_detail11split_shapeElliiliPl", I64, I64, I32, I32, I64, I32,
                   ctypes.POINTER(I64), restype=I32)
-    return "ABCDEF"[f(rows, tokens, k, CUS, ctypes.byref(I64()))]
+    return "ABCDEF"[f(rows, cols, G, k, tokens, CUS, ctypes.byref(I64()))]
 
 
 def form(rows, cols, k, tokens, G=128):
@@ -100,7 +100,7 @@ def test_decode_rule_leaves_the_batch_form_only_what_it_takes():
 
 def test_split_tests_reach_every_tile_shape():
     from test_gpu_split import EXACT
-    seen = {(G, split_shape(rows, M, k)) for rows, cols, G, M in EXACT for k in (1, 2, 3, 4)
+    seen = {(G, split_shape(rows, cols, M, k, G)) for rows, cols, G, M in EXACT for k in (1, 2, 3, 4)
             if form(rows, cols, k, M, G) == "split"}
     assert seen == {(G, s) for G in (32, 64, 128) for s in "ABCDEF"}
 
@@ -114,3 +114,17 @@ def test_prefill_tests_run_the_prefill_form():
     for rows, cols, M, k in t.SAME_ORDER:
         assert form(rows, cols, k, M) == "prefill"
         assert all(form(rows, cols, k, min(32, M - m)) == "general" for m in range(0, M, 32))
+
+
+def test_split_rule_on_many_rows():
+    """Rows whose package lines outgrow the L2: calls of few tokens leave the
+    64- and 32-token tiles that would read them with every chunk."""
+    for rows in (25600, 28672, 32000):
+        assert split_shape(rows, 4096, 24, 4, 128) != "C" and split_shape(rows, 4096, 24, 4, 64) == "E"
+    for rows, cols in ((16384, 8192), (16000, 6144)):
+        assert form(rows, cols, 4, 24) == "prefill"
+    for rows, cols, k, G in ((10922, 12288, 3, 128), (8192, 12288, 4, 128), (10885, 8192, 4, 64),
+                             (16384, 8192, 2, 64)):
+        assert form(rows, cols, k, 24, G) == "general"
+    for rows, cols, k, G in ((10885, 8192, 3, 128), (10885, 5120, 4, 64), (8192, 8192, 4, 128)):
+        assert form(rows, cols, k, 24, G) == "split"
