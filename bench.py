@@ -328,19 +328,19 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 def time_prefill(tokens=2048, ks=(4, 1),
                  shapes=((4096, 4096, "q_proj/o_proj"), (12288, 4096, "gate_proj/up_proj"),
                          (4096, 12288, "down_proj"))):
-    """rrq_linear at prefill size on the Qwen3-8B layer shapes (time_linear_shape),
-    against the bf16 matrix-core peak: the stage-sum form does k products of
-    2 M rows cols flops each (every stage on the matrix cores)."""
+    """rrq_linear at prefill size on the Qwen3-8B layer shapes (time_linear_shape):
+    the product's 2 M rows cols flops (product_tflops), and the share of the bf16
+    matrix-core peak of the passes that are run (mfma_frac): one per stage at 1
+    and 2 stages, the split form's three at 3 and 4."""
     out = {"tokens": tokens}
     for rows, cols, name in shapes:
         r = time_linear_shape(rows, cols, list(ks), [tokens])
         for key, v in r["results"].items():
             k = int(key.split("_k")[1])
-            flops = 2.0 * tokens * rows * cols * k
-            tf = flops / (v["us_per_call"] * 1e-6) / 1e12
+            tf = 2.0 * tokens * rows * cols / (v["us_per_call"] * 1e-6) / 1e12
             out[f"{rows}x{cols}_k{k}"] = {"proj": name, "us_per_call": v["us_per_call"],
-                                          "stage_tflops": round(tf, 1),
-                                          "mfma_frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4)}
+                                          "product_tflops": round(tf, 1),
+                                          "mfma_frac": round(tf * min(k, 3) / MFMA_BF16_PEAK_TFLOPS, 4)}
     return out
 
 

@@ -16,9 +16,9 @@
 // bfloat16 has binary32's range, so a value's neighbours along its row, or in
 // its tile, do not matter. Two binary16 operands and two passes took as long
 // (the activations then need converting, with running bounds on the ranges of
-// every token and row: 12288 x 4096, 2048 tokens, 4 stages 519 against 519
-// us; 5120 x 5120, 48 tokens 44.1 against 33.9) and held 22 bits of W~ at
-// best, fewer the wider the ranges.
+// every token and row: 12288 x 4096, 2048 tokens, 4 / 3 stages 519 / 490
+// against 519 / 496 us; 5120 x 5120, 48 tokens 43.2 against 30.9) and held 22
+// bits of W~ at best, fewer the wider the ranges.
 //
 // Accumulation order: the chunks of a row in 4 contiguous quarters
 // (ceil(chunks / 4) each), a quarter in stretches of 4 chunks, each
@@ -28,14 +28,19 @@
 // on which waves take the quarters: every token count gives the same results.
 // On longer rows quarters of their own waves are summed before they meet.
 //
-// What bounds it: vector issue and the matrix cores, with one or two of a
-// SIMD's waves to hide each behind the other. Per chunk of 16 rows a wave
-// forms its B operands with about 390 vector instructions at 4 stages (9 per
-// element and 3.5 to split it) whatever the tokens; a SIMD spends 4 to 5
-// cycles on each and 10 issue cycles per MFMA, of 16 the MFMA takes. So the
-// tile has as many tokens as registers and LDS allow (256: 16 accumulators
-// and 16 running sums) before it has more rows, and calls with few tiles
-// rather split the quarters over waves than the tokens.
+// What bounds it: with many tokens the matrix cores are busy half of the time,
+// and operand building, which two waves of a SIMD do not hide behind each
+// other, takes the rest (12288 x 4096, 2048 tokens, 4 stages: 538 us, 383 TFLOP/s
+// of the product, 1150 of the three passes; 777 us in the prefill form, which
+// multiplies every stage's codes). Per chunk of 16 rows a wave forms its B
+// operands with about 390 vector instructions at 4 stages (9 per element and
+// 3.5 to split it) whatever the tokens; a SIMD spends 4 to 5 cycles on each and
+// 10 issue cycles per MFMA, of 16 the MFMA takes. So the tile has as many tokens
+// as registers and LDS allow (256: 16 accumulators and 16 running sums) before
+// it has more rows. With few tokens the waves wait for their chunk's loads
+// (5120 x 5120, 48 tokens: an instruction every 9 cycles and SIMD; 30.9 us,
+// general kernel 56.6), and calls with few tiles rather split the quarters over
+// waves than the tokens.
 //
 // Tried on the binary16 operands and not kept: 32 x 32 x 16 MFMAs with two of
 // a SIMD's waves in alternate vector and matrix phases (562 us on the first
@@ -62,8 +67,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kZpSymmetric = 2;
 constexpr int kScaleF32 = 0, kScaleF16 = 1;
-// Chunks accumulated before they are folded into the running sum. Error of
-// 12288 x 4096, 2048 tokens, 4 stages / 5120 x 25600, 192 tokens, 1 stage and
+// Chunks accumulated before they are folded into the running sum. Error on
+// random packages of 12288 x 4096, 2048 tokens, 4 stages / 5120 x 25600, 192 tokens, 1 stage and
 // groups of 32, off 64 bits: 3.5e-7 / 4.5e-7 with 16 chunks, 3.5e-7 / 3.3e-7
 // with 8, 2.6e-7 / 2.6e-7 with 4, for 516 / 336, 514 / 337 and 519 / 341 us.
 constexpr uint32_t kFoldChunks = 4;
