@@ -82,6 +82,9 @@ EXACT = [
     (4090, 128, 128, 1021), (1023, 640, 128, 127), (70, 128, 128, 66),
     (4090, 352, 32, 2043), (12290, 160, 32, 30), (12290, 192, 64, 30), (12290, 128, 128, 30),
     (16700, 128, 128, 50), (4090, 256, 128, 100),
+    # row tiles no multiple of 8: with a pitch that is one, and where that would
+    # take another round
+    (2100, 192, 64, 2043), (2680, 128, 128, 79),
 ]
 
 
